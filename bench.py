@@ -609,7 +609,7 @@ def run_mxfp4(args, wl, cfg):
                              "mxfp4_GBps": round((mx_bytes(n, k) + t * (k + kb * 4 + n * 4)) / (m1 * 1e-3) / 1e9, 1),
                              "folded_GBps": round((matrix_bytes(n, k) + t * (k + kb * 4 + n * 4)) / (mf * 1e-3) / 1e9, 1)}
     ms = by_tokens["1"]["mxfp4_ms"]
-    roof = hbm_roof("gemv_mx", mx_bytes(n, k) + k + kb * 4 + n * 4, ms, "k_gemv_mx<2, 1, 2, false>")
+    roof = hbm_roof("gemv_mx", mx_bytes(n, k) + k + kb * 4 + n * 4, ms, "k_gemv_mx<2, 1, 2>")
     return dict(value=gbs, K=K, W=W, elapsed=elapsed, reps=reps, tokens=K, roof=roof,
                 config={"workload": cfg["name"], "n": n, "k": k, "tokens_per_step": 1, "bits_per_weight": 4.25,
                         "rotating_copies": copies, "format": "MXFP4 (e2m1 codes, e8m0 scale per 32), doubled-e2m1 "

@@ -1,14 +1,13 @@
-// The serving dot pass for one tq matrix (Sec. 2.2): exact int32 block sums of the
+// The serving dot pass for one tq matrix and one token (up to four on a small matrix; more
+// tokens: tq_gemv_mfma.hip) (Sec. 2.2): exact int32 block sums of the
 // folded codes against int8 block-quantized activations, then one fp32 multiply-add
 // per block.
 //
 // Decode is HBM-bound (0.5 byte of codes per weight, a few integer ops per weight per
 // token), so the kernel is shaped for the memory system: each wave owns RPW whole
 // rows, issues all of their 16-byte code loads up front (a wave load = 8 consecutive
-// blocks = 1 KB, fully coalesced), and keeps them in registers, unpacked, while it walks
-// the tokens NT at a time. A lane always covers the same columns of every row it owns
-// (block 8i + l/8, chunk l & 7 for load i), so its activations sit in registers too,
-// loaded once per token chunk. Per load, the lanes' exact 32-code partials of all
+// blocks = 1 KB, fully coalesced), and keeps them in registers. A lane always covers the same columns of every row it owns
+// (block 8i + l/8, chunk l & 7 for load i), so its activations sit in registers too. Per load, the lanes' exact 32-code partials of all
 // RPW x NT (row, token) items meet in one integer butterfly over the 8 lanes of each
 // block (exact block sums, which the debug output stores), each kept block sum gets one
 // fp32 multiply-add by f32(s) * d, and one fp32 butterfly over the blocks gives the row
@@ -20,9 +19,8 @@
 
 namespace tq {
 
-// LOOP = false: one chunk of at most NT tokens (t <= NT), no token loop, so nothing
-// loop-invariant is hoisted and kept live across it.
-template <int NL, int NT, int RPW, bool LOOP>
+// One chunk of at most NT tokens (t <= NT).
+template <int NL, int NT, int RPW>
 __global__ __launch_bounds__(256) void k_gemv(const uint8_t* __restrict__ codes,
                                               const uint16_t* __restrict__ scales, int n, int kb,
                                               const int8_t* __restrict__ q, const float* __restrict__ d, int t,
@@ -36,35 +34,32 @@ __global__ __launch_bounds__(256) void k_gemv(const uint8_t* __restrict__ codes,
   if (row0 >= n) return;
   const int64_t k = (int64_t)kb * 256;
 
-  // The activations and block scales of a chunk of NT tokens. The first chunk's are
-  // requested before the weights: a compute unit returns loads in issue order, so these
-  // small, cache-resident loads would otherwise wait behind every weight load in flight.
+  // The activations and block scales are requested before the weights: a compute unit
+  // returns loads in issue order, so these small, cache-resident loads would otherwise wait
+  // behind every weight load in flight.
   int qa[NT][NL][8];
   float dk[KI][NL];
-  auto load_acts = [&](int t0) {
 #pragma unroll
-    for (int tt = 0; tt < NT; ++tt)
+  for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
-      for (int i = 0; i < NL; ++i) {
-        const int64_t tc = min(t0 + tt, t - 1);
-        const int4* p = reinterpret_cast<const int4*>(q + tc * k + min(8 * i + g, kb - 1) * 256 + cp * 32);
-        const int4 lo = p[0], hi = p[1];
-        qa[tt][i][0] = lo.x; qa[tt][i][1] = lo.y; qa[tt][i][2] = lo.z; qa[tt][i][3] = lo.w;
-        qa[tt][i][4] = hi.x; qa[tt][i][5] = hi.y; qa[tt][i][6] = hi.z; qa[tt][i][7] = hi.w;
-      }
-    // the lane's kept items: their tokens' block scales (masked at use: a select here
-    // would make the compiler wait for these loads before issuing the weights)
-#pragma unroll
-    for (int kk = 0; kk < KI; ++kk) {
-      const int tok = t0 + RR::kept(kk, lane) % NT;
-#pragma unroll
-      for (int i = 0; i < NL; ++i) {
-        const int b = 8 * i + g;
-        dk[kk][i] = d[(int64_t)min(tok, t - 1) * kb + min(b, kb - 1)];
-      }
+    for (int i = 0; i < NL; ++i) {
+      const int64_t tc = min(tt, t - 1);
+      const int4* p = reinterpret_cast<const int4*>(q + tc * k + min(8 * i + g, kb - 1) * 256 + cp * 32);
+      const int4 lo = p[0], hi = p[1];
+      qa[tt][i][0] = lo.x; qa[tt][i][1] = lo.y; qa[tt][i][2] = lo.z; qa[tt][i][3] = lo.w;
+      qa[tt][i][4] = hi.x; qa[tt][i][5] = hi.y; qa[tt][i][6] = hi.z; qa[tt][i][7] = hi.w;
     }
-  };
-  load_acts(0);
+  // the lane's kept items: their tokens' block scales (masked at use: a select here
+  // would make the compiler wait for these loads before issuing the weights)
+#pragma unroll
+  for (int kk = 0; kk < KI; ++kk) {
+    const int tok = RR::kept(kk, lane) % NT;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int b = 8 * i + g;
+      dk[kk][i] = d[(int64_t)min(tok, t - 1) * kb + min(b, kb - 1)];
+    }
+  }
 
   // Loads are unconditional from clamped addresses (a predicated load becomes a branch
   // that serializes the loads): rows past n are computed and not stored, blocks past kb
@@ -88,45 +83,38 @@ __global__ __launch_bounds__(256) void k_gemv(const uint8_t* __restrict__ codes,
 
   __builtin_amdgcn_sched_barrier(0);  // every load above is issued before any math
 
-  // t >= 1 (the launcher returns early for t == 0): a do-while keeps the loads above
-  // in the kernel's entry block instead of sinking them under a loop guard
-  int t0 = 0;
-  do {
-    if (t0 > 0) load_acts(t0);
-    float acc[KI];
+  float acc[KI];
 #pragma unroll
-    for (int kk = 0; kk < KI; ++kk) acc[kk] = 0.0f;
+  for (int kk = 0; kk < KI; ++kk) acc[kk] = 0.0f;
 #pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      int p[RPW * NT];
+  for (int i = 0; i < NL; ++i) {
+    int p[RPW * NT];
 #pragma unroll
-      for (int r = 0; r < RPW; ++r)
+    for (int r = 0; r < RPW; ++r)
 #pragma unroll
-        for (int tt = 0; tt < NT; ++tt) {
-          int c[8];
-          unpack16c(w[r][i], c);
-          p[r * NT + tt] = dot32x16(c, qa[tt][i]);
-        }
-      RR::block_sums(p);
+      for (int tt = 0; tt < NT; ++tt) {
+        int c[8];
+        unpack16c(w[r][i], c);
+        p[r * NT + tt] = dot32x16(c, qa[tt][i]);
+      }
+    RR::block_sums(p);
 #pragma unroll
-      for (int kk = 0; kk < KI; ++kk) {
-        const int is = p[kk] >> 4;  // exact block sum of c * q
-        const int tok = t0 + RR::kept(kk, lane) % NT, b = 8 * i + g;
-        const float dv = (tok < t && b < kb) ? dk[kk][i] : 0.0f;
-        acc[kk] = fmaf(s[i] * dv, (float)is, acc[kk]);
-        if (isum_dbg != nullptr && RR::block_writer(lane)) {
-          const int row = row0 + RR::kept(kk, lane) / NT;
-          if (tok < t && row < n && b < kb) isum_dbg[((int64_t)tok * n + row) * kb + b] = is;
-        }
+    for (int kk = 0; kk < KI; ++kk) {
+      const int is = p[kk] >> 4;  // exact block sum of c * q
+      const int tok = RR::kept(kk, lane) % NT, b = 8 * i + g;
+      const float dv = (tok < t && b < kb) ? dk[kk][i] : 0.0f;
+      acc[kk] = fmaf(s[i] * dv, (float)is, acc[kk]);
+      if (isum_dbg != nullptr && RR::block_writer(lane)) {
+        const int row = row0 + RR::kept(kk, lane) / NT;
+        if (tok < t && row < n && b < kb) isum_dbg[((int64_t)tok * n + row) * kb + b] = is;
       }
     }
-    RR::block_totals(acc);
-    if (RR::writer(lane)) {
-      const int it = RR::item(lane), tok = t0 + it % NT, row = row0 + it / NT;
-      if (tok < t && row < n) y[(int64_t)tok * n + row] = acc[0];
-    }
-    t0 += NT;
-  } while (LOOP && t0 < t);
+  }
+  RR::block_totals(acc);
+  if (RR::writer(lane)) {
+    const int it = RR::item(lane), tok = it % NT, row = row0 + it / NT;
+    if (tok < t && row < n) y[(int64_t)tok * n + row] = acc[0];
+  }
 }
 
 // One token with fp32 activations, quantization fused: each workgroup quantizes x into LDS
@@ -247,17 +235,13 @@ static gemv_x_fn pick_gemv_x(int kb, int rpw) {
 using gemv_fn = void (*)(const uint8_t*, const uint16_t*, int, int, const int8_t*, const float*, int, float*,
                          int32_t*);
 
-// Four rows per wave only where a row is at most two loads (the launcher's rule).
+// Four rows per wave only for one token, where a row is at most two loads (the launcher's rule).
 template <int NL>
 static gemv_fn pick_gemv_nl(int nt, int rpw) {
-  // one token: a single pass; several: chunks of four
-  if constexpr (NL <= 2) {
-    if (nt == 1) return rpw == 1 ? k_gemv<NL, 1, 1, false> : k_gemv<NL, 1, 4, false>;
-    return rpw == 1 ? k_gemv<NL, 4, 1, true> : k_gemv<NL, 4, 4, true>;
-  } else {
-    (void)rpw;
-    return nt == 1 ? k_gemv<NL, 1, 1, false> : k_gemv<NL, 4, 1, true>;
-  }
+  if (nt == 4) return k_gemv<NL, 4, 1>;
+  if constexpr (NL <= 2)
+    if (rpw == 4) return k_gemv<NL, 1, 4>;
+  return k_gemv<NL, 1, 1>;
 }
 
 static gemv_fn pick_gemv(int nl, int nt, int rpw) {
@@ -276,11 +260,6 @@ static gemv_fn pick_gemv(int nl, int nt, int rpw) {
 }  // namespace tq
 
 namespace tq {
-// Rows per wave for large matrices when several tokens share a chunk (build-time knob).
-#ifndef TQ_GEMV_RPW_MULTI
-#define TQ_GEMV_RPW_MULTI 4
-#endif
-
 static tq_status gemv_run(const tq_mat* w, const int8_t* q, const float* d, const int32_t* bsum, int64_t t, float* y,
                           int32_t* isum_dbg, void* stream, void* const* events) {
   if (!w) return fail(TQ_ERR_INVALID, "tq_gemv: null matrix descriptor");
@@ -298,9 +277,17 @@ static tq_status gemv_run(const tq_mat* w, const int8_t* q, const float* d, cons
     return fail(TQ_ERR_ALIGN, "tq_gemv: q must be 16-byte aligned, other buffers naturally aligned");
   if ((int64_t)t * n * (k / 256) > ((int64_t)1 << 40)) return fail(TQ_ERR_INVALID, "tq_gemv: problem too large");
   const int kb = k / 256, nl = (kb + 7) / 8;
+  // Several tokens: the matrix cores, except where the matrix is too small to fill them and
+  // one chunk of four tokens does (4 tokens, k = 4096: 3.95 against 4.25 us at 2048 rows,
+  // 5.48 against 4.47 at 4096; k = 16384: 6.1 against 8.1 at 512 rows, 11.6 against 8.4 at 2048).
+  if (t > 4 || (t > 1 && (n > 2048 || (int64_t)n * kb > 65536))) {
+    (void)hipGetLastError();
+    launch_gemv_mfma(0, w->codes, w->scales, n, kb, q, d, (int)t, y, isum_dbg, (hipStream_t)stream, events);
+    return check_launch("tq_gemv");
+  }
   const int nt = t == 1 ? 1 : 4;
   // Few rows: one row per wave, to spread a small matrix over all CUs.
-  const int rpw = (n >= 16384 && nl <= 2) ? (nt == 1 ? 4 : TQ_GEMV_RPW_MULTI) : 1;
+  const int rpw = (n >= 16384 && nl <= 2) ? 4 : 1;
   const int64_t waves = (n + rpw - 1) / rpw;
   const unsigned wgs = (unsigned)((waves + 3) / 4);
   (void)hipGetLastError();

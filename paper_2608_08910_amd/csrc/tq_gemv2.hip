@@ -5,33 +5,17 @@
 // Same memory plan as the folded pass: a 256-weight block is 128 bytes of trits (two
 // planes x 2 bits), 8 lanes per block, a wave's 16-byte load covers 8 consecutive blocks
 // (1 KB, coalesced), and each wave owns RPW whole rows whose loads are all issued up
-// front. The two planes of a chunk share its 32 activations: per chunk a lane forms
+// front. (One token, or up to four on a small matrix; more tokens: tq_gemv_mfma.hip.) The two planes of a chunk share its 32 activations: per chunk a lane forms
 // both planes' exact partials (64t bytes against q), the integer butterfly carries the
 // pair per (row, token) item, and the lane that keeps an item applies the block's two
 // scales, plane 1's multiply-add before plane 2's.
 #include <hip/hip_ext.h>
 
+#include "tq_decode.hpp"
 #include "tq_device.hpp"
 #include "tq_internal.hpp"
 
 namespace tq {
-
-// Free-scale two-plane chunks: the 16 bytes of chunk j hold plane 1's 32 trits in bytes
-// 0..7 and plane 2's in bytes 8..15; within a plane's two dwords, dword u, byte b, bit
-// pair 2s..2s+1 is column 32j + 16u + 4s + b as a 2-bit two's-complement trit (00 = 0,
-// 01 = +1, 11 = -1). Shifting the pair to a byte's top bits and masking leaves 64*t as a
-// signed byte, so a plane decodes in one or two bitwise operations per activation dword
-// and the byte dot's sum is exactly 64 times the trit dot.
-constexpr uint32_t kTopPairs = 0xC0C0C0C0u;
-
-// One plane's 32 trits (dwords w0, w1) as 64t bytes in the order of the activation
-// dwords: t[4u + s] = columns 16u + 4s .. 16u + 4s + 3.
-__device__ __forceinline__ void unpack64t(uint32_t w0, uint32_t w1, int (&t)[8]) {
-  t[0] = int((w0 << 6) & kTopPairs); t[1] = int((w0 << 4) & kTopPairs);
-  t[2] = int((w0 << 2) & kTopPairs); t[3] = int(w0 & kTopPairs);
-  t[4] = int((w1 << 6) & kTopPairs); t[5] = int((w1 << 4) & kTopPairs);
-  t[6] = int((w1 << 2) & kTopPairs); t[7] = int(w1 & kTopPairs);
-}
 
 // Both planes' partials of one 16-byte chunk against 32 int8 activations: exact
 // multiples of 64 (|.| <= 32 * 64 * 127 per chunk; a whole block stays below 2^21, and
@@ -168,19 +152,16 @@ __global__ __launch_bounds__(256) void k_gemv2(const uint8_t* __restrict__ codes
 using gemv2_fn = void (*)(const uint8_t*, const uint32_t*, int, int, const int8_t*, const float*, int, float*,
                           int32_t*);
 
-// Register budget (the launcher's rules): four rows per wave only where a row is at
-// most two loads, four tokens per chunk only where a row is at most four loads.
+// Register budget: four rows per wave only for one token where a row is at most two loads,
+// four tokens at once only where a row is at most four loads (longer rows walk them).
 template <int NL>
 static gemv2_fn pick_gemv2_nl(int nt, int rpw, bool one) {
-  if constexpr (NL <= 2) {
-    if (nt == 1) return rpw == 1 ? k_gemv2<NL, 1, 1, false> : k_gemv2<NL, 1, 4, false>;
-    return rpw == 1 ? k_gemv2<NL, 4, 1, true> : k_gemv2<NL, 4, 4, true>;
-  } else if constexpr (NL <= 4) {
-    (void)rpw;
-    return nt == 1 ? k_gemv2<NL, 1, 1, false> : k_gemv2<NL, 4, 1, true>;
+  if constexpr (NL <= 4) {
+    if (nt == 4) return k_gemv2<NL, 4, 1, false>;
+    if constexpr (NL <= 2)
+      if (rpw == 4) return k_gemv2<NL, 1, 4, false>;
+    return k_gemv2<NL, 1, 1, false>;
   } else {
-    (void)rpw;
-    (void)nt;
     return one ? k_gemv2<NL, 1, 1, false> : k_gemv2<NL, 1, 1, true>;
   }
 }
@@ -198,11 +179,6 @@ static gemv2_fn pick_gemv2(int nl, int nt, int rpw, bool one) {
   }
 }
 
-// Rows per wave for large matrices when several tokens share a chunk (build-time knob).
-#ifndef TQ_GEMV2_RPW_MULTI
-#define TQ_GEMV2_RPW_MULTI 1
-#endif
-
 static tq_status gemv2_run(const tq_mat2* w, const int8_t* q, const float* d, int64_t t, float* y, int32_t* isum_dbg,
                            void* stream, void* const* events) {
   if (!w) return fail(TQ_ERR_INVALID, "tq_gemv2: null matrix descriptor");
@@ -219,8 +195,16 @@ static tq_status gemv2_run(const tq_mat2* w, const int8_t* q, const float* d, in
     return fail(TQ_ERR_ALIGN, "tq_gemv2: q must be 16-byte and scales 4-byte aligned, other buffers naturally aligned");
   if ((int64_t)t * n * (k / 256) > ((int64_t)1 << 39)) return fail(TQ_ERR_INVALID, "tq_gemv2: problem too large");
   const int kb = k / 256, nl = (kb + 7) / 8;
+  // Several tokens: the matrix cores, except where the matrix is too small to fill them and
+  // one chunk of four tokens does (4 tokens, k = 4096: 4.20 against 4.30 us at 2048 rows,
+  // 5.94 against 4.44 at 4096; k = 16384, 2 tokens: 5.7 against 8.0 at 512 rows, 10.9 against 8.5 at 2048).
+  if (t > 4 || (t > 1 && (n > 2048 || (int64_t)n * kb > 65536))) {
+    (void)hipGetLastError();
+    launch_gemv_mfma(1, w->codes, w->scales, n, kb, q, d, (int)t, y, isum_dbg, (hipStream_t)stream, events);
+    return check_launch("tq_gemv2");
+  }
   const int nt = (t == 1 || nl > 4) ? 1 : 4;
-  const int rpw = (n >= 16384 && nl <= 2) ? (nt == 1 ? 4 : TQ_GEMV2_RPW_MULTI) : 1;
+  const int rpw = (n >= 16384 && nl <= 2) ? 4 : 1;
   const int64_t waves = (n + rpw - 1) / rpw;
   const unsigned wgs = (unsigned)((waves + 3) / 4);
   const uint32_t* sc = reinterpret_cast<const uint32_t*>(w->scales);

@@ -24,4 +24,9 @@ constexpr int kMaxK = 16384;
 hipError_t launch_quantize(const float* x, int64_t t, int32_t k, int8_t* q, float* d, int32_t* bsum,
                            hipStream_t st);
 
+// The several-token dot pass of one matrix (fmt 0 folded, 1 two planes, 2 MXFP4); events:
+// null or a start and a stop event.
+void launch_gemv_mfma(int fmt, const uint8_t* codes, const void* scales, int n, int kb, const int8_t* q, const float* d,
+                      int t, float* y, int32_t* isum_dbg, hipStream_t st, void* const* events);
+
 }  // namespace tq

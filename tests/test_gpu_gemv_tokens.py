@@ -1,0 +1,72 @@
+"""The several-token dot pass on the matrix cores (tq_gemv, tq_gemv2, tq_gemv_mx with more
+than one token) against the single-token kernels on the same quantized activations.
+
+Bar: exact block sums equal and y bitwise equal, token by token: both take each row's fp32
+block terms in the same order (the single-token kernels' own parity with the oracle is
+asserted in their tests)."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import announce, device
+from test_gpu_gemv import gpu_quantize
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def tq():
+    device()
+    from paper_2608_08910_amd import tq as _tq
+    return _tq
+
+
+def make(tq, fmt, n, k, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    kb = k // 256
+    codes = torch.randint(0, 256, (n, kb, 128), dtype=torch.uint8, device="cuda", generator=g)
+    if fmt == "folded":
+        lo, hi = codes % 9, (codes // 16) % 9  # nine levels per nibble, as 4-bit two's complement
+        codes = ((lo + 12) & 15) | (((hi + 12) & 15) << 4)
+        m = tq.TqMatrix(n, k, codes, (torch.rand((n, kb), device="cuda", generator=g) + 0.01).half().view(torch.int16))
+        return m, lambda q, d, y, s: tq.tq_gemv(m, q, d, torch.zeros(d.shape, dtype=torch.int32, device="cuda"), y, s), (kb,)
+    if fmt == "twoplane":
+        codes &= 0x55 | ((codes & 0x55) << 1)  # no 2-bit code 2: a trit is 0, 1 or 3
+        a = (torch.rand((n, kb, 2), device="cuda", generator=g) - 0.3).half().view(torch.int16)
+        m = tq.TqMatrix2(n, k, codes, a)
+        return m, lambda q, d, y, s: tq.tq_gemv2(m, q, d, y, s), (kb, 2)
+    e8 = torch.randint(110, 130, (n * kb * 8 + 1,), dtype=torch.uint8, device="cuda", generator=g)
+    m = tq.TqMatrixMx(n, k, codes, e8[1:].view(n, kb * 8))  # scales off any alignment
+    return m, lambda q, d, y, s: tq.tq_gemv_mx(m, q, d, y, s), (kb * 8,)
+
+
+# every tile of the dispatch (16-token x 16-row tiles 1x1, 1x2, 2x1, 2x2, 2x4, 4x4) with
+# ragged rows and tokens; rows of 1 to 64 blocks (one, two, four and eight waves per row
+# tile, waves with no block, ragged last rounds); 2 to 4 tokens on both sides of the small-
+# matrix bound
+SHAPES = [(70, 1280, 5), (16, 256, 16), (300, 512, 17), (131, 768, 33), (45, 1024, 64), (8205, 1280, 7), (4107, 2304, 17),
+          (8205, 1280, 20), (16397, 2048, 31), (2061, 4352, 509), (16397, 1536, 65), (37, 16384, 130), (2049, 256, 2),
+          (2048, 4096, 3), (4099, 4096, 4), (33, 16384, 4), (40007, 256, 40), (1, 256, 300)]
+
+
+@pytest.mark.parametrize("fmt", ["folded", "twoplane", "mxfp4"])
+@pytest.mark.parametrize("n,k,t", SHAPES)
+def test_tokens_match_single_token_calls_bitwise(tq, fmt, n, k, t):
+    announce(f"{fmt} tokens n={n} k={k} t={t}")
+    m, call, per = make(tq, fmt, n, k, n + k + t)
+    x = np.random.default_rng(t).standard_normal((t, k)).astype(np.float32)
+    q, d, _ = gpu_quantize(tq, x * np.exp(np.linspace(-3, 3, t, dtype=np.float32))[:, None])
+    y = torch.full((t + 1, n), float("nan"), device="cuda")
+    call(q, d, y[:t], None)
+    s = torch.full((t, n, *per), -1, dtype=torch.int32, device="cuda")
+    ys = torch.full((t, n), float("nan"), device="cuda")
+    call(q, d, ys, s)
+    assert torch.equal(y[:t], ys), "debug output changes y"
+    assert bool(torch.isnan(y[t]).all()), "written past the last token"
+    for i in sorted({0, 1, t // 2, min(15, t - 1), min(16, t - 1), t - 2, t - 1}):
+        y1 = torch.full((1, n), float("nan"), device="cuda")
+        s1 = torch.full((1, n, *per), -1, dtype=torch.int32, device="cuda")
+        call(q[i:i + 1], d[i:i + 1], y1, s1)
+        assert torch.equal(s[i], s1[0]), f"block sums of token {i}"
+        assert torch.equal(y[i], y1[0]), f"y of token {i}"
