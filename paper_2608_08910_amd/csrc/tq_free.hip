@@ -79,25 +79,91 @@ __device__ __forceinline__ uint16_t f16_sat(float x) {
   return __builtin_bit_cast(uint16_t, (_Float16)(fabsf(x) >= 65520.0f ? c : x));
 }
 
-__global__ __launch_bounds__(256) void k_free_quantize(const float* __restrict__ w, int64_t nblocks, int max_iter,
-                                                       const uint8_t* __restrict__ tcodes,
-                                                       const uint16_t* __restrict__ tscales,
-                                                       uint8_t* __restrict__ codes2, uint32_t* __restrict__ scales2,
-                                                       uint8_t* __restrict__ iters) {
-#pragma clang fp contract(off)
-  __shared__ uint32_t s_w[16][32];  // per block: the 128 two-plane bytes as dwords
-  const int lane = threadIdx.x & 63, grp = lane >> 4, u = lane & 15;
-  const int lb = (threadIdx.x >> 6) * 4 + grp;
-  const int64_t blk0 = (int64_t)blockIdx.x * 16, blk = min(blk0 + lb, nblocks - 1);
-  const bool real = blk0 + lb < nblocks;  // a group past the last block repeats it, stores nothing
-  for (int i = threadIdx.x; i < 16 * 32; i += 256) (&s_w[0][0])[i] = 0u;
-  const float* wb = w + blk * 256;
-  float v[kFreeE];
+// Sum over the 16 lanes of a group (whole numbers: any order).
+__device__ __forceinline__ int group16_sum(int v) {
+  v = group_sum_i32(v);
+  return v + __builtin_amdgcn_update_dpp(0, v, kDppRowRor8, 0xf, 0xf, false);
+}
+
+// A weight's plane pair for |w| (both trits change sign with w) as one word: bits 31:30 t2 and
+// 29:28 t1 in two's complement; below them what a sum over the block's weights counts: bit 0
+// t1 != 0, bit 6 t2 != 0, bit 12 trits of opposite direction, bit 18 of the same, relative to
+// the signs of (a1, a2).
+// a * b + c in one instruction (24-bit operands; the compiler splits it into a multiply and a
+// three-operand add)
+__device__ __forceinline__ int mad24(int a, int b, int c) {
+  int r;
+  asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+
+constexpr uint32_t kPairMask = 0xF0000000u;
+__device__ __forceinline__ uint32_t trit2(int t) { return (uint32_t)t & 3u; }
+// the pair's four top bits for w of either sign
+__device__ __forceinline__ uint32_t pair_signed(uint32_t x, float w) {
+  return (int)__float_as_uint(w) < 0 ? x ^ ((x & 5u) << 1) : x;
+}
+
+// The plane step by thresholds on |w|. With A = |a1| > B = |a2| > 0 the candidates are 0 and
+// +- the four levels B, A - B, A, A + B; with every gap at least 2^-16 of the block's largest
+// magnitude, all differences w - candidate near a decision are exact in fp64, so the nearest
+// candidate changes at the exact middle of two neighbouring levels and a tie goes to the
+// pair that comes first in the order 0, -1, +1: the one with the zero trit, whatever the
+// signs. T[i] is the smallest fp32 |w| (as bits) that takes level i + 1, K[i] that level's
+// pair. (Otherwise `ok` is false, and the wave's blocks take the nine-candidate search.)
+struct Levels {
+  uint32_t T[4], K[4];
+  bool ok;
+};
+
+__device__ __forceinline__ Levels make_levels(float a1, float a2, float amax) {
+  Levels L;
+  const float A = fabsf(a1), B = fabsf(a2);
+  const float tol = 0x1p-16f * fmaxf(amax, A + B);
+  L.ok = (B >= 0x1p-100f) & (B >= tol) & (A - B >= tol) & (fabsf((A - B) - B) >= tol) & (tol < 0x1p100f);
+  const double dA = A, dB = B, dD = dA - dB;
+  const bool c = dB < dD;
+  const double l2 = c ? dD : dB;
+  const double M[4] = {0.5 * (c ? dB : dD), 0.5 * dA, 0.5 * (l2 + dA), dA + 0.5 * dB};
+  const bool down[4] = {true, c, !c, true};  // the lower level takes a tie
 #pragma unroll
-  for (int j = 0; j < kFreeE; ++j) v[j] = wb[u + 16 * j];
-  // the tied fit: weight u + 32m in the low nibble of byte 16m + u, u + 32m + 16 in the high
+  for (int i = 0; i < 4; ++i) {
+    const float f = (float)M[i];
+    L.T[i] = __float_as_uint(f) + (uint32_t)(((double)f < M[i]) | (((double)f == M[i]) & down[i]));
+  }
+  const int s1 = (int)__float_as_uint(a1) < 0 ? -1 : 1, s2 = (int)__float_as_uint(a2) < 0 ? -1 : 1;
+  const uint32_t kA = (trit2(s1) << 28) | 1u, kB = (trit2(s2) << 30) | (1u << 6);
+  const uint32_t kD = (trit2(s1) << 28) | (trit2(-s2) << 30) | 1u | (1u << 6) | (1u << 12);
+  L.K[0] = c ? kB : kD;
+  L.K[1] = c ? kD : kB;
+  L.K[2] = kA;
+  L.K[3] = (kA | kB) + (1u << 18);
+  return L;
+}
+
+__device__ __forceinline__ uint32_t level_pair(uint32_t aw, const Levels& L) {
+  uint32_t k = aw >= L.T[0] ? L.K[0] : 0u;
+  k = aw >= L.T[1] ? L.K[1] : k;
+  k = aw >= L.T[2] ? L.K[2] : k;
+  return aw >= L.T[3] ? L.K[3] : k;
+}
+
+// One lane's share of a block: its pairs (t1 in bits 1:0, t2 in bits 3:2), the scale pair and
+// the plane steps.
+struct FreeFit {
+  uint32_t x[kFreeE];
+  uint16_t h1, h2;
+  int it;
+};
+
+// The alternation for any block (every lane of the wave): scale sums in the pairwise-halving
+// order, the nine-candidate plane step.
+__device__ __forceinline__ void free_fit_general(const float (&v)[kFreeE], const uint8_t* cb, float s, int grp, int u,
+                                                 int max_iter, FreeFit& F) {
+#pragma clang fp contract(off)
   int t1[kFreeE], t2[kFreeE];
-  const uint8_t* cb = tcodes + blk * 128;
+  uint16_t h1 = 0, h2 = 0;
+  // the tied fit: weight u + 32m in the low nibble of byte 16m + u, u + 32m + 16 in the high
 #pragma unroll
   for (int m = 0; m < kFreeE / 2; ++m) {
     const int byte = cb[16 * m + u];
@@ -110,7 +176,6 @@ __global__ __launch_bounds__(256) void k_free_quantize(const float* __restrict__
       t2[2 * m + h] = c - 3 * a;
     }
   }
-  const float s = f16_bits_to_f32(tscales[blk]);
   const bool live = s != 0.0f;  // uniform within the group
   float a1 = 3.0f * s, a2 = s;
   int it = 0;
@@ -157,7 +222,6 @@ __global__ __launch_bounds__(256) void k_free_quantize(const float* __restrict__
       done = same || it == max_iter;
     }
   }
-  uint16_t h1 = 0, h2 = 0;
   if (live) {
     h1 = f16_sat(a1);
     h2 = f16_sat(a2);
@@ -166,22 +230,174 @@ __global__ __launch_bounds__(256) void k_free_quantize(const float* __restrict__
 #pragma unroll
     for (int j = 0; j < kFreeE; ++j) t1[j] = t2[j] = 0;
   }
-  __syncthreads();  // s_w cleared
-  // pack: weight u + 16j is column 32 (j / 2) + 16 (j % 2) + 4 (u / 4) + (u % 4) of its
-  // block, i.e. plane p's dword 4 (j / 2) + 2p + (j % 2), bits 8 (u % 4) + 2 (u / 4)
-  const int sh = 8 * (u & 3) + 2 * (u >> 2);
+#pragma unroll
+  for (int j = 0; j < kFreeE; ++j) F.x[j] = trit2(t1[j]) | (trit2(t2[j]) << 2);
+  F.h1 = h1;
+  F.h2 = h2;
+  F.it = it;
+}
+
+// The same by thresholds, with the same result, where every live block of the wave has well
+// separated levels at every step and no tiny weight with a trit in its tied fit (false
+// otherwise). Every weight with a trit is then past 2^-17 of the block's largest, so with
+// amax < 2^(e+1) it is a multiple of 2^(e-41): |w| = (hi 2^20 + lo) 2^(e-41), and the sums of
+// a scale step are exact in whole numbers (as the general path's are in fp64).
+__device__ __forceinline__ bool free_fit_levels(const float (&v)[kFreeE], const uint8_t* cb, float s, int grp, int u,
+                                                int max_iter, FreeFit& F) {
+#pragma clang fp contract(off)
+  uint32_t amaxb = 0;
+#pragma unroll
+  for (int j = 0; j < kFreeE; ++j) amaxb = max(amaxb, __float_as_uint(fabsf(v[j])));
+  amaxb = max(amaxb, (uint32_t)lane_xor_i<8>((int)amaxb));
+  amaxb = max(amaxb, (uint32_t)lane_xor_i<4>((int)amaxb));
+  amaxb = max(amaxb, (uint32_t)lane_xor_i<2>((int)amaxb));
+  amaxb = max(amaxb, (uint32_t)lane_xor_i<1>((int)amaxb));
+  const float amax = __uint_as_float(amaxb);
+  const int e = (int)(amaxb >> 23) - 127;
+  const bool live = s != 0.0f;  // uniform within the group
+  bool bad = amaxb >= 0x7F800000u;  // infinities and NaN
+  int hi[kFreeE], lo[kFreeE];
 #pragma unroll
   for (int j = 0; j < kFreeE; ++j) {
-    atomicOr(&s_w[lb][4 * (j >> 1) + (j & 1)], (uint32_t)(t1[j] & 3) << sh);
-    atomicOr(&s_w[lb][4 * (j >> 1) + 2 + (j & 1)], (uint32_t)(t2[j] & 3) << sh);
+    const float x = ldexpf(fabsf(v[j]), 21 - e);
+    hi[j] = (int)x;  // below 2^22
+    lo[j] = (int)((x - (float)hi[j]) * 0x1p20f);
   }
+  // the tied fit's planes (folded onto |w|) and their sums: weight u + 32m in the low nibble of
+  // byte 16m + u, u + 32m + 16 in the high
+  uint32_t kw[kFreeE];
+  int suh = 0, sul = 0, svh = 0, svl = 0, sa = 0, sb = 0, sc = 0;
+  const float least = 0x1p-17f * amax;
+#pragma unroll
+  for (int m = 0; m < kFreeE / 2; ++m) {
+    const int byte = cb[16 * m + u];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int j = 2 * m + h;
+      int c = (int)((uint32_t)byte << (28 - 4 * h)) >> 28;
+      bad |= (c < -4) | (c > 4) | ((c != 0) & (fabsf(v[j]) < least));
+      c = (int)__float_as_uint(v[j]) < 0 ? -c : c;
+      const int t1 = (c >= 2 ? 1 : 0) - (c <= -2 ? 1 : 0), t2 = c - 3 * t1;  // balanced-ternary digits
+      kw[j] = (trit2(t1) << 28) | (trit2(t2) << 30);
+      suh = mad24(hi[j], t1, suh);
+      sul = mad24(lo[j], t1, sul);
+      svh = mad24(hi[j], t2, svh);
+      svl = mad24(lo[j], t2, svl);
+      sa += t1 * t1;
+      sb += t1 * t2;
+      sc += t2 * t2;
+    }
+  }
+  if (__any(bad & live)) return false;
+  sa = group16_sum(sa);
+  sb = group16_sum(sb);
+  sc = group16_sum(sc);
+  float a1 = 3.0f * s, a2 = s;
+  int it = 0;
+  bool done = !live;  // a group stops at its own stopping point; the wave runs until all do
+  while (!__all(done)) {
+    // scale step: least squares for (a1, a2) given the planes
+    const double su = ldexp((double)group16_sum(suh) * 0x1p20 + (double)group16_sum(sul), e - 41);
+    const double sv = ldexp((double)group16_sum(svh) * 0x1p20 + (double)group16_sum(svl), e - 41);
+    const int det = sa * sc - sb * sb;  // |.| <= 256^2: exact in int
+    if (!done && det > 0) {
+      const double num1 = (double)sc * su - (double)sb * sv;
+      const double num2 = (double)sa * sv - (double)sb * su;
+      a1 = (float)(num1 / (double)det);
+      a2 = (float)(num2 / (double)det);
+    }
+    // plane step, with the sums and counts of the next scale step
+    const Levels L = make_levels(a1, a2, amax);
+    if (!__all(L.ok | done)) return false;
+    uint32_t diff = 0, cnt = 0;
+    suh = sul = svh = svl = 0;
+#pragma unroll
+    for (int j = 0; j < kFreeE; ++j) {
+      const uint32_t k = level_pair(__float_as_uint(fabsf(v[j])), L);
+      const int t1 = (int)(k << 2) >> 30, t2 = (int)k >> 30;
+      suh = mad24(hi[j], t1, suh);
+      sul = mad24(lo[j], t1, sul);
+      svh = mad24(hi[j], t2, svh);
+      svl = mad24(lo[j], t2, svl);
+      cnt += k;  // (fields of 6 bits, at most 16 each)
+      diff |= k ^ kw[j];
+      kw[j] = k;
+    }
+    const uint64_t unchanged = __ballot((diff & kPairMask) == 0);
+    const bool same = ((unchanged >> (16 * grp)) & 0xFFFFu) == 0xFFFFu;
+    if (!done) {
+      ++it;
+      done = same || it == max_iter;
+    }
+    const int c02 = group16_sum((int)((cnt & 63u) | ((cnt << 4) & 0x3F0000u)));
+    const int c13 = group16_sum((int)(((cnt >> 6) & 63u) | ((cnt >> 2) & 0x3F0000u)));
+    sa = c02 & 0xFFFF;
+    sc = c13 & 0xFFFF;
+    sb = (c13 >> 16) - (c02 >> 16);
+    sb = (int)(__float_as_uint(a1) ^ __float_as_uint(a2)) < 0 ? -sb : sb;
+  }
+  F.it = it;
+  F.h1 = live ? f16_sat(a1) : 0;
+  F.h2 = live ? f16_sat(a2) : 0;
+  const Levels L = make_levels(f16_bits_to_f32(F.h1), f16_bits_to_f32(F.h2), amax);
+  if (!__all(L.ok | !live)) return false;
+  const uint32_t keep = live ? kPairMask : 0u;
+#pragma unroll
+  for (int j = 0; j < kFreeE; ++j) {
+    F.x[j] = pair_signed((level_pair(__float_as_uint(fabsf(v[j])), L) & keep) >> 28, v[j]);
+  }
+  return true;
+}
+
+// Bound by the vector ALU over the iterations of the alternation. Per weight and iteration the
+// threshold step is 17 operations (compares and selects of the pair, four whole-number
+// multiply-adds, the count, the change test), where the nine-candidate search with its products takes about 60 operations:
+// 2048 x 4096 82 us, the search alone 242. (A wave runs until its slowest of four blocks stops:
+// 6.9 iterations, 3.5 a block on average.)
+__global__ __launch_bounds__(256) void k_free_quantize(const float* __restrict__ w, int64_t nblocks, int max_iter,
+                                                       const uint8_t* __restrict__ tcodes,
+                                                       const uint16_t* __restrict__ tscales,
+                                                       uint8_t* __restrict__ codes2, uint32_t* __restrict__ scales2,
+                                                       uint8_t* __restrict__ iters) {
+#pragma clang fp contract(off)
+  __shared__ __attribute__((aligned(16))) uint8_t s_w[16][128];  // per block: the two-plane bytes
+  const int lane = threadIdx.x & 63, grp = lane >> 4, u = lane & 15;
+  const int lb = (threadIdx.x >> 6) * 4 + grp;
+  const int64_t blk0 = (int64_t)blockIdx.x * 16, blk = min(blk0 + lb, nblocks - 1);
+  const bool real = blk0 + lb < nblocks;  // a group past the last block repeats it, stores nothing
+  const float* wb = w + blk * 256;
+  float v[kFreeE];
+#pragma unroll
+  for (int j = 0; j < kFreeE; ++j) v[j] = wb[u + 16 * j];
+  const float s = f16_bits_to_f32(tscales[blk]);
+  const uint8_t* cb = tcodes + blk * 128;
+  FreeFit F;
+  if (!free_fit_levels(v, cb, s, grp, u, max_iter, F)) free_fit_general(v, cb, s, grp, u, max_iter, F);
+  // pack: weight u + 16j is column 32 (j / 2) + 16 (j % 2) + 4 (u / 4) + (u % 4) of its
+  // block, i.e. plane p's dword 4 (j / 2) + 2p + (j % 2), byte u % 4, bits 2 (u / 4). The four
+  // lanes of a byte (u, u ^ 4, u ^ 8, u ^ 12) join their bits (16 bytes a plane, four j to a
+  // dword), and each stores the bytes of j = 4i + u / 4.
+  const int q4 = u >> 2;
+#pragma unroll
+  for (int p = 0; p < 2; ++p)
+#pragma unroll
+    for (int i = 0; i < kFreeE / 4; ++i) {
+      uint32_t z = 0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) z |= ((F.x[4 * i + k] >> (2 * p)) & 3u) << (8 * k);
+      z <<= 2 * q4;
+      z |= (uint32_t)lane_xor_i<4>((int)z);
+      z |= (uint32_t)lane_xor_i<8>((int)z);
+      const int j = 4 * i + q4;
+      s_w[lb][(4 * (j >> 1) + 2 * p + (j & 1)) * 4 + (u & 3)] = (uint8_t)(z >> (8 * q4));
+    }
   __syncthreads();
   const int t = threadIdx.x;
   if (t < 128 && blk0 + (t >> 3) < nblocks)
     reinterpret_cast<uint4*>(codes2 + (blk0 + (t >> 3)) * 128)[t & 7] = reinterpret_cast<const uint4*>(s_w[t >> 3])[t & 7];
   if (u == 0 && real) {
-    scales2[blk] = (uint32_t)h1 | ((uint32_t)h2 << 16);
-    if (iters) iters[blk] = (uint8_t)it;
+    scales2[blk] = (uint32_t)F.h1 | ((uint32_t)F.h2 << 16);
+    if (iters) iters[blk] = (uint8_t)F.it;
   }
 }
 

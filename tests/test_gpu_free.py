@@ -65,6 +65,39 @@ def test_free_edge_blocks(tq, oracle, max_iter):
     assert it[0].max() == 0 and it[1].max() == 0
 
 
+def value_blocks(kind: str, n: int, k: int) -> np.ndarray:
+    rng = np.random.default_rng(len(kind) * 131 + n)
+    w = rng.standard_normal((n, k))
+    if kind == "grid":  # exact ties between levels and with their middles
+        w = rng.integers(-9, 10, (n, k)) / 8.0 * 2.0 ** rng.integers(-6, 7, (n, 1))
+    elif kind == "two-level":  # planes that fit exactly: levels on the weights, A = 2B and B > A
+        w = rng.choice([-3.0, -2.0, -1.0, 1.0, 2.0, 3.0], (n, k)) * rng.choice([1.0, 0.7], (n, 1))
+    elif kind == "sparse":
+        w *= rng.random((n, k)) < 0.08
+    elif kind == "outlier":  # one weight far past the rest: the others lose their trits
+        w[:, ::256] *= 10.0 ** rng.integers(0, 7, (n, 1))
+    elif kind == "wide":  # magnitudes over many orders within a block
+        w *= np.exp(rng.standard_normal((n, k)) * 5)
+    elif kind == "tiny":  # scales that are f16-subnormal or underflow to zero
+        w *= 2.0 ** rng.integers(-40, -8, (n, 1))
+    elif kind == "mixed":  # blocks of every kind side by side in one wave
+        kinds = ["grid", "two-level", "sparse", "outlier", "wide", "tiny", "normal"]
+        v = [value_blocks(x, n, k) for x in kinds]
+        pick = rng.integers(0, len(kinds), (n, k // 256))
+        w = np.stack(v)[np.repeat(pick, 256, axis=1), np.arange(n)[:, None], np.arange(k)[None, :]]
+    return np.ascontiguousarray(w, dtype=np.float32)
+
+
+@pytest.mark.parametrize("kind", ["normal", "grid", "two-level", "sparse", "outlier", "wide", "tiny", "mixed"])
+def test_free_thresholds_and_search_agree_with_the_oracle(tq, oracle, kind):
+    # the threshold plane step and the nine-candidate search it falls back to, on blocks at
+    # the line between them; 37 x 5 blocks leave the last wave's groups part-empty
+    w = value_blocks(kind, 37, 1280)
+    announce(f"free values {kind}")
+    check(tq, oracle, w)
+    check(tq, oracle, w, max_iter=3)
+
+
 def test_free_full_matrix_deterministic(tq, oracle):
     c = gen.QUANT_CONFIG
     w = gen.float_weights(gen.SEED, 0, c["n"], c["k"])
