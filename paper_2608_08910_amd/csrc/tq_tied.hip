@@ -21,7 +21,7 @@ constexpr int kTiedE = 16;  // weights per lane
 // correctly rounded quotient. Past |q| = 8 the clamp decides alone, so a fixed margin of
 // 2^-18 covers every q that matters. The few elements that near a half-integer (exact
 // ties among them) take the division.
-__device__ __forceinline__ void tied_code_step(const float (&w)[kTiedE], float s, int (&c)[kTiedE]) {
+__device__ __forceinline__ void tied_code_step(const float (&w)[kTiedE], float s, float (&c)[kTiedE]) {
   const float rs = 1.0f / s;
   float r[kTiedE];
   bool near = false;
@@ -39,7 +39,7 @@ __device__ __forceinline__ void tied_code_step(const float (&w)[kTiedE], float s
     }
   }
 #pragma unroll
-  for (int j = 0; j < kTiedE; ++j) c[j] = (int)__builtin_amdgcn_fmed3f(r[j], -4.0f, 4.0f);
+  for (int j = 0; j < kTiedE; ++j) c[j] = __builtin_amdgcn_fmed3f(r[j], -4.0f, 4.0f);
 }
 
 // a + (the lane-pair partner's a), for a butterfly over lane bit M (both lanes of a pair
@@ -49,11 +49,11 @@ __device__ __forceinline__ double xor_add(double a) {
   const int lo = __double2loint(a), hi = __double2hiint(a);
   return a + __hiloint2double(lane_xor_i<M>(hi), lane_xor_i<M>(lo));
 }
-template <int M>
-__device__ __forceinline__ int xor_add(int a) {
-  return a + lane_xor_i<M>(a);
-}
 
+// Bound by the vector ALU over the iterations (13.4 a block, and a wave runs until its slowest
+// of four blocks stops: 15.8). Codes stay fp32 whole numbers from the rounding to the sums: no
+// conversion to int, <c, c> by fp32 multiply-adds (exact: at most 4096). 2048 x 4096: 47.7 us,
+// 58.8 with integer codes and products.
 __global__ __launch_bounds__(256) void k_tied_quantize(const float* __restrict__ w, int64_t nblocks, int max_iter,
                                                        uint8_t* __restrict__ codes, uint16_t* __restrict__ scales,
                                                        uint8_t* __restrict__ iters) {
@@ -73,58 +73,49 @@ __global__ __launch_bounds__(256) void k_tied_quantize(const float* __restrict__
   amax = fmaxf(amax, __int_as_float(lane_xor_i<4>(__float_as_int(amax))));
   amax = fmaxf(amax, __int_as_float(lane_xor_i<2>(__float_as_int(amax))));
   amax = fmaxf(amax, __int_as_float(lane_xor_i<1>(__float_as_int(amax))));
-  int c[kTiedE];
-#pragma unroll
-  for (int j = 0; j < kTiedE; ++j) c[j] = 0;
+  float c[kTiedE];
   const bool live = amax >= 0x1p-100f;  // uniform within the group
   float s = amax / 4.0f;
   int it = 0;
   bool done = !live;  // a group stops at its own stopping point; the wave runs until all do
-  {
-    int prev[kTiedE];
 #pragma unroll
-    for (int j = 0; j < kTiedE; ++j) prev[j] = 0;
-    while (true) {
-      int cn[kTiedE];
-      tied_code_step(v, s, cn);
-      int diff = 0;
+  for (int j = 0; j < kTiedE; ++j) c[j] = 0.0f;
+  while (true) {
+    float cn[kTiedE];
+    tied_code_step(v, s, cn);
+    bool diff = false;
 #pragma unroll
-      for (int j = 0; j < kTiedE; ++j) {
-        diff |= cn[j] ^ prev[j];
-        if (!done) c[j] = cn[j];
-      }
-      const uint64_t unchanged = __ballot(diff == 0);
-      const bool same = ((unchanged >> (16 * grp)) & 0xFFFFu) == 0xFFFFu;
-      if (!done) {
-        ++it;
-        done = (it > 1 && same) || it == max_iter;
-      }
-      if (__all(done)) break;
-      // <w, c> in fp64 (exact products), pairwise halving: within the lane h = 128 .. 16,
-      // across the group h = 8 .. 1; <c, c> exact
-      double p[kTiedE];
-#pragma unroll
-      for (int j = 0; j < kTiedE; ++j) p[j] = (double)v[j] * (double)c[j];
-#pragma unroll
-      for (int h = kTiedE / 2; h >= 1; h >>= 1)
-#pragma unroll
-        for (int j = 0; j < h; ++j) p[j] = p[j] + p[j + h];
-      double num = xor_add<8>(p[0]);
-      num = xor_add<4>(num);
-      num = xor_add<2>(num);
-      num = xor_add<1>(num);
-      int cc = 0;
-#pragma unroll
-      for (int j = 0; j < kTiedE; ++j) cc += c[j] * c[j];
-      cc = xor_add<8>(cc);
-      cc = xor_add<4>(cc);
-      cc = xor_add<2>(cc);
-      cc = xor_add<1>(cc);
-#pragma unroll
-      for (int j = 0; j < kTiedE; ++j) prev[j] = c[j];
-      if (!done && cc != 0) s = (float)(num / (double)cc);
-      if (!done && cc == 0) done = true;
+    for (int j = 0; j < kTiedE; ++j) {
+      diff |= cn[j] != c[j];
+      c[j] = cn[j];
     }
+    const uint64_t changed = __ballot(diff);
+    const bool same = ((changed >> (16 * grp)) & 0xFFFFu) == 0;
+    if (!done) {
+      ++it;
+      done = (it > 1 && same) || it == max_iter;
+    }
+    if (__all(done)) break;
+    // <w, c> in fp64 (exact products), pairwise halving: within the lane h = 128 .. 16,
+    // across the group h = 8 .. 1; <c, c> exact
+    double p[kTiedE];
+#pragma unroll
+    for (int j = 0; j < kTiedE; ++j) p[j] = (double)v[j] * (double)c[j];
+#pragma unroll
+    for (int h = kTiedE / 2; h >= 1; h >>= 1)
+#pragma unroll
+      for (int j = 0; j < h; ++j) p[j] = p[j] + p[j + h];
+    double num = xor_add<8>(p[0]);
+    num = xor_add<4>(num);
+    num = xor_add<2>(num);
+    num = xor_add<1>(num);
+    float c2 = 0.0f;
+#pragma unroll
+    for (int j = 0; j < kTiedE; ++j) c2 = fmaf(c[j], c[j], c2);
+    int cc = group_sum_i32((int)c2);
+    cc += __builtin_amdgcn_update_dpp(0, cc, kDppRowRor8, 0xf, 0xf, false);
+    if (!done && cc != 0) s = (float)(num / (double)cc);
+    if (!done && cc == 0) done = true;
   }
   uint16_t h16 = 0;
   if (live) {
@@ -134,19 +125,19 @@ __global__ __launch_bounds__(256) void k_tied_quantize(const float* __restrict__
     const float sd = (float)hs;
     if (sd == 0.0f) {
 #pragma unroll
-      for (int j = 0; j < kTiedE; ++j) c[j] = 0;
+      for (int j = 0; j < kTiedE; ++j) c[j] = 0.0f;
     } else {
       tied_code_step(v, sd, c);
     }
   } else {
 #pragma unroll
-    for (int j = 0; j < kTiedE; ++j) c[j] = 0;
+    for (int j = 0; j < kTiedE; ++j) c[j] = 0.0f;
   }
   // pack: weight u + 32m (j = 2m) takes the low nibble of byte 16m + u, weight u + 32m + 16
   // (j = 2m + 1) its high nibble
 #pragma unroll
   for (int m = 0; m < kTiedE / 2; ++m)
-    s_bytes[lb][16 * m + u] = (uint8_t)((c[2 * m] & 15) | ((c[2 * m + 1] & 15) << 4));
+    s_bytes[lb][16 * m + u] = (uint8_t)(((int)c[2 * m] & 15) | (((int)c[2 * m + 1] & 15) << 4));
   __syncthreads();
   // 16 blocks x 128 bytes: lanes write 16 bytes each
   const int t = threadIdx.x;
