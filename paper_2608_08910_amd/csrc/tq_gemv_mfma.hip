@@ -10,7 +10,8 @@
 // (no barrier in the loop, each streams its own bytes), a small matrix still puts eight
 // waves on every row tile, and each sum is taken in exactly the order of the single-token
 // kernels (lane group g of those takes the blocks b mod 8 = g, then an xor butterfly), so
-// a token's result has the same bits whatever kernel took it. Rows of fewer than five
+// a token's result has the same bits whatever kernel took it (MXFP4 aside, whose block sums
+// are taken another way, below). Rows of fewer than five
 // blocks use fewer waves per row tile (a power of two >= kb) and more row tiles.
 //
 // Per block a wave loads its rows' codes and its tokens' activations row-coalesced (a row
@@ -62,8 +63,56 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
-__device__ __forceinline__ float lane_get(float v, int src) {
-  return __int_as_float(__builtin_amdgcn_ds_bpermute(src << 2, __float_as_int(v)));
+// ---------------------------------------------------------------------------------
+// MXFP4 on the scaled fp8 x fp4 MFMA. The released bytes are its fp4 operand as they are: a
+// lane's 16-byte chunk is 32 codes with their own e8m0 scale. The int8 activations go in as
+// two fp8 (e4m3) operands, q = 16 h + l with l = q & 15 and h = q >> 4: both at most four
+// significant bits, so exact, as is every product, and the unit adds them in fp32, without
+// rounding while a row block's scales span at most 2^8 (short of extreme codes and activations
+// throughout); measured against 64 bits: 5.0e-8 to 5.7e-8 of the result's norm, 6.8e-8 to
+// 7.4e-8 from whole-number sums scaled chunk by chunk. A wave with a wider span takes those.
+// They need a decode of every code and a scaling of every 32-element sum: 32768 x 4096, 4 tokens: 21 us, 28 so (VALU pass
+// 38.4); 2048 x 4096, 509 tokens: 25 us, 49 so (VALU pass 151).
+// ---------------------------------------------------------------------------------
+
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ uint32_t max_u16x2(uint32_t a, uint32_t b) {
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+
+// Four table entries by the 4-bit index whose low three bits are in the bytes of idx7 (0..7)
+// and whose top bit is bit 7 of the bytes of top.
+__device__ __forceinline__ int lut16(uint32_t t0, uint32_t t1, uint32_t t2, uint32_t t3, uint32_t idx7, uint32_t top) {
+  const uint32_t p = __builtin_amdgcn_perm(t1, t0, idx7), n = __builtin_amdgcn_perm(t3, t2, idx7);
+  const uint32_t m = __builtin_amdgcn_perm(top, top << 8, kSignSel);
+  return (int)((n & m) | (p & ~m));
+}
+// Four signed bytes q as fp8: l = q & 15 (0 .. 15; e4m3's bytes 0 .. 15 are the values
+// 0 .. 15 times 2^-9 as they are) and h = q >> 4 (-8 .. 7).
+constexpr int kLoScale = 127 + 9, kHiScale = 127 + 4;
+__device__ __forceinline__ int fp8_lo(uint32_t q) { return (int)(q & 0x0F0F0F0Fu); }
+__device__ __forceinline__ int fp8_hi(uint32_t q) {
+  return lut16(0x44403800u, 0x4E4C4A48u, 0xCACCCED0u, 0xB8C0C4C8u, (q >> 4) & 0x07070707u, q);
+}
+
+// A lane's operand of the tokens for one MFMA of 128 columns (four chunks). The lane (li, g)
+// of an fp8 operand holds K positions 16 g .. 16 g + 15 and 64 + 16 g .., so half hf is bytes
+// 8 (g & 1) .. + 7 of both 16-byte columns (a: elements 0..15, b: 16..31) of chunk
+// 2 hf + (g >> 1), in the order of the chunk's nibbles (element i, then 16 + i).
+__device__ __forceinline__ void mx_acts(const uint2 a, const uint2 b, int hf, v8i& lo, v8i& hi) {
+  const uint32_t av[2] = {a.x, a.y}, bv[2] = {b.x, b.y};
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    const uint32_t e0 = __builtin_amdgcn_perm(bv[m], av[m], 0x05010400u);
+    const uint32_t e1 = __builtin_amdgcn_perm(bv[m], av[m], 0x07030602u);
+    lo[4 * hf + 2 * m] = fp8_lo(e0);
+    lo[4 * hf + 2 * m + 1] = fp8_lo(e1);
+    hi[4 * hf + 2 * m] = fp8_hi(e0);
+    hi[4 * hf + 2 * m + 1] = fp8_hi(e1);
+  }
 }
 
 // The partial results of the workgroup's waves -> y. 2^lnw waves share a row tile.
@@ -86,15 +135,17 @@ __device__ __forceinline__ void dm_combine(const uint8_t* s_wave, int lnw, int64
   }
 }
 
-// FMT 0: folded codes, f16 scales. FMT 1: two planes, f16 scale pairs. DBG: the instance that
+// FMT 0: folded codes, f16 scales. FMT 1: two planes, f16 scale pairs. FMT 2: MXFP4, e8m0
+// scales. DBG: the instance that
 // stores the exact block sums (so that the others carry no store addresses).
 template <int FMT, int MTT, int RT, bool DBG>
-__global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(MTT == 1 && !DBG ? 4 : 2))) void k_gemv_mfma(
+__global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(MTT == 1 && FMT != 2 && !DBG ? 4 : 2))) void k_gemv_mfma(
     const uint8_t* __restrict__ codes, const void* __restrict__ scales, int n, int kb, int lnw,
     const int8_t* __restrict__ q, const float* __restrict__ d, int t, float* __restrict__ y,
     int32_t* __restrict__ isum_dbg) {
   using S = DmShape<MTT, RT>;
-  constexpr int NP = FMT == 1 ? 2 : 1, SH = FMT == 1 ? 6 : 4, SB = FMT == 1 ? 4 : 2;
+  constexpr bool MX = FMT == 2;
+  constexpr int NP = FMT == 1 ? 2 : 1, SH = FMT == 1 ? 6 : 4, SB = MX ? 8 : (FMT == 1 ? 4 : 2);
   constexpr int AUX = MTT == 1 ? kBufNT : 0;  // up to 16 tokens each weight byte is read once
   constexpr int NB = MTT <= 2 && RT > 1 ? 2 : 1;  // row tiles in LDS at once
   __shared__ __attribute__((aligned(16))) uint8_t s_wave[kDmWaves * S::kWave];
@@ -123,6 +174,7 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
   const uint32_t vw = (uint32_t)((lane >> 3) * kb * 128 + (lane & 7) * 16);
   const uint32_t vd = lane < S::TOK ? (uint32_t)(lane * kb * 4) : kDmOob;
   const uint32_t vs = lane < S::ROWS ? (uint32_t)(lane * kb * SB) : kDmOob;
+  const uint32_t ve = (uint32_t)(li * kb * 8 + g);
 
   for (int tt = blockIdx.y; (int64_t)tt * S::TOK < t; tt += gridDim.y) {
     const int t0 = tt * S::TOK, ntok = min(S::TOK, t - t0);
@@ -134,7 +186,9 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
     // read as zero, with no memory access. Scalar offsets stay below the resource's size (rows
     // and blocks clamped), as its range check subtracts them; a block past kb takes kDmOob as
     // the lane's offset.
+    constexpr int kAfterX = MX ? 4 * RT + 1 : 2 * RT + 2;  // loads per block issued after the activations'
     uint4 W[RT][2];
+    uint32_t E[MX ? RT : 1][2];  // MXFP4: the scales of row 16 rt + li, chunks g and 4 + g (bytes: any alignment)
     uint32_t sc;
     float dd;
     const auto fetch_x = [&](int b) {
@@ -146,7 +200,14 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
     const auto fetch_sd = [&](int b) {
       const uint32_t so = (uint32_t)min(b, kb - 1);
       dd = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(dr, b < kb ? vd : kDmOob, so * 4u, 0));
-      if constexpr (FMT == 1) sc = __builtin_amdgcn_raw_buffer_load_b32(sr, b < kb ? vs : kDmOob, so * SB, 0);
+      if constexpr (MX) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+          for (int c = 0; c < 2; ++c)
+            E[rt][c] = __builtin_amdgcn_raw_buffer_load_b8(sr, b < kb ? ve + 4 * c : kDmOob,
+                                                           (uint32_t)(min(16 * rt, nrows - 1) * kb + min(b, kb - 1)) * 8u, 0);
+      } else if constexpr (FMT == 1) sc = __builtin_amdgcn_raw_buffer_load_b32(sr, b < kb ? vs : kDmOob, so * SB, 0);
       else sc = buf_load_u16(sr, b < kb ? vs : kDmOob, so * SB);
     };
     const auto fetch_w = [&](int b, int rt) {
@@ -170,29 +231,61 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
 #pragma unroll
         for (int v = 0; v < 4; ++v) acc[mt][rt][v] = 0.0f;
 
-    for (int b = kg; b < kb; b += kDmWaves) {
-      wait_vmcnt<2 * RT + 2>();  // the block's activations are in LDS (its scales and codes may not be here yet)
+    bool exact = MX && DBG;  // MXFP4: the wave takes the exact pass below instead
+    for (int b = kg; b < kb && !exact; b += kDmWaves) {
+      wait_vmcnt<kAfterX>();  // the block's activations are in LDS (its scales and codes may not be here yet)
       wave_lds_fence();
-      v4i aop[MTT][2][2];
+      v4i aop[MX ? 1 : MTT][2][2];
+      uint2 xa[MX ? MTT : 1][2][2], xb[MX ? MTT : 1][2][2];
 #pragma unroll
       for (int mt = 0; mt < MTT; ++mt)
 #pragma unroll
         for (int c = 0; c < 2; ++c)
 #pragma unroll
-          for (int h = 0; h < 2; ++h)
-            aop[mt][c][h] = *reinterpret_cast<const v4i*>(sa + (mt * 16 + li) * 256 + (((2 * (4 * c + g) + h) ^ li) * 16));
+          for (int h = 0; h < 2; ++h) {
+            const uint8_t* const row = sa + (mt * 16 + li) * 256;
+            if constexpr (MX) {
+              const int col = 2 * (4 * c + 2 * h + (g >> 1));
+              xa[mt][c][h] = *reinterpret_cast<const uint2*>(row + ((col ^ li) * 16) + 8 * (g & 1));
+              xb[mt][c][h] = *reinterpret_cast<const uint2*>(row + (((col + 1) ^ li) * 16) + 8 * (g & 1));
+            } else {
+              aop[mt][c][h] = *reinterpret_cast<const v4i*>(row + (((2 * (4 * c + g) + h) ^ li) * 16));
+            }
+          }
       ssd[lane] = __float_as_uint(dd);
-      ssd[64 + lane] = sc;
+      if constexpr (!MX) ssd[64 + lane] = sc;
       wave_lds_fence();
       float4 d4[MTT];
 #pragma unroll
       for (int mt = 0; mt < MTT; ++mt) d4[mt] = *reinterpret_cast<const float4*>(&ssd[mt * 16 + 4 * g]);
       uint32_t scr[RT];
+      if constexpr (!MX) {
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) scr[rt] = ssd[64 + rt * 16 + li];
+        for (int rt = 0; rt < RT; ++rt) scr[rt] = ssd[64 + rt * 16 + li];
+      }
       wave_lds_fence();
       __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));  // LDS reads done: the area may be refilled
       wave_lds_fence();
+      // MXFP4: the block's scales, and whether a row's span more than 2^8 (its fp32 sums could
+      // then round where the whole-number sums do not) or any is outside 2^+-63 (they could
+      // overflow, or lose bits that d brings back). Halves: E and 255 - E, maxima over the
+      // row's eight chunks.
+      uint32_t es[MX ? RT : 1][2];
+      if constexpr (MX) {
+        bool far = false;
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+          es[rt][0] = E[rt][0];
+          es[rt][1] = E[rt][1];
+          const auto halves = [](uint32_t e) { return e * 0xFFFF0001u + 0x00FF0000u; };  // e | (255 - e) << 16
+          uint32_t m = max_u16x2(halves(es[rt][0]), halves(es[rt][1]));
+          m = max_u16x2(m, (uint32_t)lane_xor_i<16>((int)m));
+          m = max_u16x2(m, (uint32_t)lane_xor_i<32>((int)m));
+          const uint32_t hi = m & 0xFFFFu, lo = 255u - (m >> 16);
+          far |= (rt * 16 + li < nrows) & ((hi > 190u) | (lo < 64u) | (hi - lo > 8u));
+        }
+        exact = __any(far) != 0;
+      }
       fetch_x(b + kDmWaves);
       __builtin_amdgcn_sched_barrier(0);
       fetch_sd(b + kDmWaves);
@@ -211,6 +304,44 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
         wt[rt & 1][1] = *reinterpret_cast<const uint4*>(p + li * 128 + (((4 + g) ^ rs) * 16));
         fetch_w(b + kDmWaves, rt);
       };
+      if constexpr (MX) {
+        if (exact) break;
+        {
+          v8i alo[MTT][2], ahi[MTT][2];
+#pragma unroll
+          for (int mt = 0; mt < MTT; ++mt)
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+              for (int h = 0; h < 2; ++h) mx_acts(xa[mt][c][h], xb[mt][c][h], h, alo[mt][c], ahi[mt][c]);
+          stage_w(0);
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) {
+            if (rt + 1 < RT) stage_w(rt + 1);
+            v4f C[MTT];
+#pragma unroll
+            for (int mt = 0; mt < MTT; ++mt) C[mt] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+              const uint4 w = wt[rt & 1][c];
+              const v8i bw = {(int)w.x, (int)w.y, (int)w.z, (int)w.w, 0, 0, 0, 0};
+#pragma unroll
+              for (int mt = 0; mt < MTT; ++mt)
+                C[mt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(alo[mt][c], bw, C[mt], 0, 4, 0, kLoScale, 0, (int)es[rt][c]);
+#pragma unroll
+              for (int mt = 0; mt < MTT; ++mt)
+                C[mt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ahi[mt][c], bw, C[mt], 0, 4, 0, kHiScale, 0, (int)es[rt][c]);
+            }
+#pragma unroll
+            for (int mt = 0; mt < MTT; ++mt) {
+              const float dv[4] = {d4[mt].x, d4[mt].y, d4[mt].z, d4[mt].w};
+#pragma unroll
+              for (int v = 0; v < 4; ++v) acc[mt][rt][v] = fmaf(dv[v], C[mt][v], acc[mt][rt][v]);
+            }
+          }
+        }
+        continue;
+      }
       stage_w(0);
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
@@ -220,8 +351,8 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
         for (int c = 0; c < 2; ++c) {
           const uint4 w = wt[rt & 1][c];
           int u[8];
-          if constexpr (FMT == 0) unpack16c(w, u);
-          else unpack64t(w.x, w.y, u);
+          if constexpr (FMT == 1) unpack64t(w.x, w.y, u);
+          else unpack16c(w, u);
           bop[0][c][0] = v4i{u[0], u[1], u[2], u[3]};
           bop[0][c][1] = v4i{u[4], u[5], u[6], u[7]};
           if constexpr (FMT == 1) {
@@ -273,6 +404,66 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
         }
       }
     }
+    if constexpr (MX) {
+      if (exact) {
+        // exact int8 sums per chunk, scaled one by one: lane (li, g) takes dword g of every
+        // 16 bytes (low nibbles: elements 4g .. 4g + 3, high nibbles: 16 + 4g ..)
+#pragma unroll
+        for (int mt = 0; mt < MTT; ++mt)
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[mt][rt][v] = 0.0f;
+        for (int b = kg; b < kb; b += kDmWaves) {
+          wait_vmcnt<0>();
+          wave_lds_fence();
+          fetch_x(b);
+          fetch_sd(b);
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) fetch_w(b, rt);
+          wait_vmcnt<0>();
+          ssd[lane] = __float_as_uint(dd);
+          wave_lds_fence();
+          float4 d4[MTT];
+#pragma unroll
+          for (int mt = 0; mt < MTT; ++mt) d4[mt] = *reinterpret_cast<const float4*>(&ssd[mt * 16 + 4 * g]);
+#pragma unroll
+          for (int rt = 0; rt < RT; ++rt) {
+            const int wr = lane >> 3, rs = (li >> 1) & 7;
+            wave_lds_fence();
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+              *reinterpret_cast<uint4*>(bt0 + (8 * c + wr) * 128 + (((lane & 7) ^ (((8 * c + wr) >> 1) & 7)) * 16)) = W[rt][c];
+            wave_lds_fence();
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll 1
+            for (int j = 4 * c; j < 4 * c + 4; ++j) {
+              const uint32_t x = *reinterpret_cast<const uint32_t*>(bt0 + li * 128 + ((j ^ rs) * 16) + 4 * g);
+              const int ex = __builtin_amdgcn_ds_bpermute((16 * (j & 3) + li) << 2, (int)E[rt][c]) - 128;
+              const uint32_t blo = (uint32_t)mx_dec4(x & 0x07070707u, x << 4), bhi = (uint32_t)mx_dec4((x >> 4) & 0x07070707u, x);
+#pragma unroll
+              for (int mt = 0; mt < MTT; ++mt) {
+                const uint8_t* const row = sa + (mt * 16 + li) * 256 + 4 * g;
+                const uint32_t a0 = *reinterpret_cast<const uint32_t*>(row + (((2 * j) ^ li) * 16));
+                const uint32_t a1 = *reinterpret_cast<const uint32_t*>(row + (((2 * j + 1) ^ li) * 16));
+                const v4i C = __builtin_amdgcn_mfma_i32_16x16x32_i8(
+                    (long)(a0 | ((uint64_t)a1 << 32)), (long)(blo | ((uint64_t)bhi << 32)), v4i{0, 0, 0, 0}, 0, 0, 0);
+                const float dv[4] = {d4[mt].x, d4[mt].y, d4[mt].z, d4[mt].w};
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                  acc[mt][rt][v] = fmaf(ldexpf(dv[v], ex), (float)C[v], acc[mt][rt][v]);
+                  const int tok = mt * 16 + 4 * g + v, r = rt * 16 + li;
+                  if (DBG && tok < ntok && row0 + r < n)
+                    isum_dbg[((int64_t)(t0 + tok) * n + row0 + r) * (kb * 8) + b * 8 + j] = C[v];
+                }
+              }
+            }
+          }
+          wave_lds_fence();
+        }
+      }
+    }
     // (the last, empty refills of the activations have landed before the area is reused)
     wait_vmcnt<0>();
     wave_lds_fence();
@@ -286,173 +477,6 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
     __syncthreads();
     dm_combine<MTT, RT>(s_wave, lnw, wg_row0, n, t0, t, y);
     __syncthreads();  // the next token tile's activations take the partial results' place
-  }
-}
-
-// MXFP4: a 16-byte chunk is one block of 32 with its own scale, so each 16x16x32 MFMA is
-// one block's exact sums, scaled into the chunk's own accumulator (the single-token kernel's
-// lane: chunk cp of the blocks b mod 8 = g), the eight of which are summed as
-// ((0+1)+(2+3))+((4+5)+(6+7)) after the last block. Lane (li, g) takes dword g of each
-// chunk: its low nibbles are columns 4g .. 4g + 3 and its high nibbles columns 16 + 4g ..,
-// so the LDS areas hold dword-transposed rows: [row][dword g][chunk].
-template <int MTT, int RT, bool DBG>
-__global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_gemv_mfma_mx(
-    const uint8_t* __restrict__ codes, const uint8_t* __restrict__ scales, int n, int kb, int lnw,
-    const int8_t* __restrict__ q, const float* __restrict__ d, int t, float* __restrict__ y,
-    int32_t* __restrict__ isum_dbg) {
-  using S = DmShape<MTT, RT>;
-  constexpr int AUX = MTT == 1 ? kBufNT : 0;
-  __shared__ __attribute__((aligned(16))) uint8_t s_wave[kDmWaves * S::kWave];
-  __shared__ __attribute__((aligned(16))) uint8_t s_bt[kDmWaves * 2048];
-  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int li = lane & 15, g = lane >> 4;
-  const int kg = wv & ((1 << lnw) - 1);
-  const int64_t wg_row0 = (int64_t)blockIdx.x * (S::ROWS << (3 - lnw));
-  const int64_t row0 = wg_row0 + (wv >> lnw) * S::ROWS;
-  const int64_t rowc = min(row0, (int64_t)n - 1);
-  const int nrows = (int)min((int64_t)S::ROWS, n - rowc);
-  const __amdgpu_buffer_rsrc_t cr = make_rsrc(codes + rowc * kb * 128, (uint32_t)(nrows * kb * 128));
-  const __amdgpu_buffer_rsrc_t sr = make_rsrc(scales + rowc * kb * 8, (uint32_t)(nrows * kb * 8));
-  uint8_t* const sa = s_wave + wv * S::kWave;
-  uint8_t* const bt = s_bt + wv * 2048;
-  // lane offsets of the loads below
-  const uint32_t vx = (uint32_t)(g * kb * 256 + li * 16), vw = (uint32_t)((lane >> 3) * kb * 128 + (lane & 7) * 16);
-  const uint32_t vd = lane < S::TOK ? (uint32_t)(lane * kb * 4) : kDmOob;
-  const uint32_t ve = (uint32_t)(li * kb * 8 + 2 * g);
-
-  for (int tt = blockIdx.y; (int64_t)tt * S::TOK < t; tt += gridDim.y) {
-    const int t0 = tt * S::TOK, ntok = min(S::TOK, t - t0);
-    const __amdgpu_buffer_rsrc_t qr = make_rsrc(q + (int64_t)t0 * kb * 256, (uint32_t)(ntok * kb * 256));
-    const __amdgpu_buffer_rsrc_t dr = make_rsrc(d + (int64_t)t0 * kb, (uint32_t)(ntok * kb * 4));
-    uint4 X[4 * MTT], W[RT][2];
-    uint32_t E[RT][2];  // scale bytes: lane (li, g) loads chunks 2g and 2g + 1 of row li
-    float dd;
-    // Scalar offsets stay below the resource's size (rows and blocks clamped), as its range
-    // check subtracts them; a block past kb takes kDmOob as the lane's offset.
-    const auto fetch_x = [&](int b) {
-      const uint32_t vo = b < kb ? vx : kDmOob;
-#pragma unroll
-      for (int e = 0; e < 4 * MTT; ++e)
-        X[e] = buf_load16(qr, vo, (uint32_t)((min(4 * e, ntok - 1) * kb + min(b, kb - 1)) * 256), 0);
-      dd = __uint_as_float(
-          __builtin_amdgcn_raw_buffer_load_b32(dr, b < kb ? vd : kDmOob, (uint32_t)min(b, kb - 1) * 4u, 0));
-    };
-    const auto fetch_w = [&](int b, int rt) {
-      // (bytes: the scales have no alignment)
-#pragma unroll
-      for (int c = 0; c < 2; ++c)
-        E[rt][c] = __builtin_amdgcn_raw_buffer_load_b8(
-            sr, b < kb ? ve + c : kDmOob, (uint32_t)((min(16 * rt, nrows - 1) * kb + min(b, kb - 1)) * 8), 0);
-#pragma unroll
-      for (int c = 0; c < 2; ++c)
-        W[rt][c] = buf_load16(cr, b < kb ? vw : kDmOob,
-                              (uint32_t)((min(16 * rt + 8 * c, nrows - 1) * kb + min(b, kb - 1)) * 128), AUX);
-    };
-    fetch_x(kg);
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) fetch_w(kg, rt);
-    __builtin_amdgcn_sched_barrier(0);
-
-    float acc[8][MTT][RT][4];
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-#pragma unroll
-      for (int mt = 0; mt < MTT; ++mt)
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) acc[j][mt][rt][v] = 0.0f;
-
-    for (int b = kg; b < kb; b += kDmWaves) {
-      // activations: dword u of 16-byte column c of row r at dword
-      // 64 r + 16 ((u + r) & 3) + 4 ((c >> 2) ^ ((r >> 2) & 3)) + (c & 3)  (reads and writes
-      // both touch every bank once)
-      uint32_t* const saw = reinterpret_cast<uint32_t*>(sa);
-#pragma unroll
-      for (int e = 0; e < 4 * MTT; ++e) {
-        const int r = 4 * e + g;
-        const uint32_t xs[4] = {X[e].x, X[e].y, X[e].z, X[e].w};
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          saw[64 * r + 16 * ((u + r) & 3) + 4 * ((li >> 2) ^ ((r >> 2) & 3)) + (li & 3)] = xs[u];
-      }
-      wave_lds_fence();
-      v4i av[MTT][4];  // dword i of av[mt][m]: column 4m + i's dword g
-#pragma unroll
-      for (int mt = 0; mt < MTT; ++mt)
-#pragma unroll
-        for (int m = 0; m < 4; ++m)
-          av[mt][m] = *reinterpret_cast<const v4i*>(saw + 64 * (mt * 16 + li) + 16 * ((g + li) & 3) + 4 * (m ^ ((li >> 2) & 3)));
-      float d4[MTT][4];
-#pragma unroll
-      for (int mt = 0; mt < MTT; ++mt)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) d4[mt][v] = lane_get(dd, mt * 16 + 4 * g + v);
-      fetch_x(b + kDmWaves);
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        // codes: dword u of chunk x of row r at dword
-        // 32 r + 8 ((u + (r >> 1)) & 3) + (x ^ (4 * ((r >> 3) & 1)))
-        uint32_t* const btw = reinterpret_cast<uint32_t*>(bt);
-        wave_lds_fence();
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const int r = 8 * c + (lane >> 3), x = lane & 7;
-          const uint32_t ws[4] = {W[rt][c].x, W[rt][c].y, W[rt][c].z, W[rt][c].w};
-#pragma unroll
-          for (int u = 0; u < 4; ++u) btw[32 * r + 8 * ((u + (r >> 1)) & 3) + (x ^ (4 * c))] = ws[u];
-        }
-        wave_lds_fence();
-        v4i wt[2];
-#pragma unroll
-        for (int m = 0; m < 2; ++m)
-          wt[m] = *reinterpret_cast<const v4i*>(btw + 32 * li + 8 * ((g + (li >> 1)) & 3) + 4 * (m ^ (li >> 3)));
-        // the row's eight scale bytes: chunk j's from lane (li, j / 2)
-        const int epair = (int)(E[rt][0] | (E[rt][1] << 16));
-        int ej[4];
-#pragma unroll
-        for (int m = 0; m < 4; ++m) ej[m] = __builtin_amdgcn_ds_bpermute((16 * m + li) << 2, epair);
-        fetch_w(b + kDmWaves, rt);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const uint32_t w = (uint32_t)wt[j >> 2][j & 3];
-          const int lo = mx_dec4(w & 0x07070707u, w << 4), hi = mx_dec4((w >> 4) & 0x07070707u, w);
-          const long bop = (long)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
-          const int ex = ((j & 1) ? (ej[j >> 1] >> 16) : (ej[j >> 1] & 0xFFFF)) - 128;
-#pragma unroll
-          for (int mt = 0; mt < MTT; ++mt) {
-            const uint32_t a0 = (uint32_t)av[mt][j >> 1][2 * (j & 1)], a1 = (uint32_t)av[mt][j >> 1][2 * (j & 1) + 1];
-            const long aop = (long)(((uint64_t)a1 << 32) | a0);
-            const v4i C = __builtin_amdgcn_mfma_i32_16x16x32_i8(aop, bop, v4i{0, 0, 0, 0}, 0, 0, 0);
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-              acc[j][mt][rt][v] = fmaf(ldexpf(d4[mt][v], ex), (float)C[v], acc[j][mt][rt][v]);
-            if constexpr (DBG) {
-#pragma unroll
-              for (int v = 0; v < 4; ++v) {
-                const int tok = mt * 16 + 4 * g + v, r = rt * 16 + li;
-                if (tok < ntok && row0 + r < n) isum_dbg[((int64_t)(t0 + tok) * n + row0 + r) * (kb * 8) + b * 8 + j] = C[v];
-              }
-            }
-          }
-        }
-      }
-    }
-    wave_lds_fence();
-    float* const pw = reinterpret_cast<float*>(sa);
-#pragma unroll
-    for (int mt = 0; mt < MTT; ++mt)
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const auto a = [&](int j) { return acc[j][mt][rt][v]; };
-          pw[(mt * 16 + 4 * g + v) * S::PS + rt * 16 + li] =
-              ((a(0) + a(1)) + (a(2) + a(3))) + ((a(4) + a(5)) + (a(6) + a(7)));
-        }
-    __syncthreads();
-    dm_combine<MTT, RT>(s_wave, lnw, wg_row0, n, t0, t, y);
-    __syncthreads();
   }
 }
 
@@ -472,11 +496,12 @@ void launch_gemv_mfma(int fmt, const uint8_t* codes, const void* scales, int n, 
   // workgroups), 5.6 at 2 x 1 (256), 6.2 at 2 x 2 (128), 8.3 at 2 x 4; 8192 x 4096, 128
   // tokens: 37.6 at 1 x 1, 18.3 at 2 x 4, 15.2 at 4 x 4). A larger tile reads fewer bytes per
   // output; one of more 16-token tiles than t fills computes padding. (Two planes: 4 x 4
-  // does not fit the registers.)
+  // does not fit the registers. MXFP4: the activations' split into fp8 pairs costs as much as four row tiles' MFMAs, so 1 x 4 beats 1 x 2 at 16
+  // tokens and fewer: 21 against 24 us at 32768 x 4096, 4 tokens.)
   struct Tile { int mtt, rt; };
   static constexpr Tile kTiles[] = {{4, 4}, {2, 4}, {2, 2}, {2, 1}, {1, 2}, {1, 1}};
-  static constexpr Tile kTilesMx[] = {{2, 1}, {1, 2}, {1, 1}};
-  const Tile* tiles = fmt == 2 ? kTilesMx : (fmt == 1 ? kTiles + 1 : kTiles);
+  static constexpr Tile kTilesMx[] = {{2, 4}, {2, 2}, {2, 1}, {1, 4}, {1, 2}, {1, 1}};
+  const Tile* tiles = fmt == 2 ? kTilesMx : (fmt == 0 ? kTiles : kTiles + 1);
   const auto wgs = [&](int rt) { return ((((int64_t)n + 16 * rt - 1) / (16 * rt)) + (1 << (3 - lnw)) - 1) >> (3 - lnw); };
   const auto ttiles = [&](int mtt) { return ((int64_t)t + 16 * mtt - 1) / (16 * mtt); };
   while ((tiles->mtt > 1 && t <= 8 * tiles->mtt) || (tiles->mtt * tiles->rt > 1 && wgs(tiles->rt) * ttiles(tiles->mtt) < 256))
@@ -486,13 +511,9 @@ void launch_gemv_mfma(int fmt, const uint8_t* codes, const void* scales, int n, 
   // several token tiles: a multiple of 8 row tiles, so that a row tile's workgroups share an XCD
   const int64_t gx = ntt > 1 ? (wgs(rt) + 7) / 8 * 8 : wgs(rt);
   const dim3 grid((unsigned)gx, (unsigned)(ntt < 16384 ? ntt : 16384));
-  const uint8_t* s8 = reinterpret_cast<const uint8_t*>(scales);
 #define TQ_DM(F, M, R)                                                                                                  \
   dm_launch(isum_dbg ? k_gemv_mfma<F, M, R, true> : k_gemv_mfma<F, M, R, false>, grid, st, events, codes, scales, n, kb, \
             lnw, q, d, t, y, isum_dbg)
-#define TQ_DX(M, R)                                                                                                     \
-  dm_launch(isum_dbg ? k_gemv_mfma_mx<M, R, true> : k_gemv_mfma_mx<M, R, false>, grid, st, events, codes, s8, n, kb, lnw, \
-            q, d, t, y, isum_dbg)
   switch (fmt * 100 + mtt * 10 + rt) {
     case 11: TQ_DM(0, 1, 1); break;
     case 12: TQ_DM(0, 1, 2); break;
@@ -505,12 +526,14 @@ void launch_gemv_mfma(int fmt, const uint8_t* codes, const void* scales, int n, 
     case 121: TQ_DM(1, 2, 1); break;
     case 122: TQ_DM(1, 2, 2); break;
     case 124: TQ_DM(1, 2, 4); break;
-    case 211: TQ_DX(1, 1); break;
-    case 212: TQ_DX(1, 2); break;
-    default: TQ_DX(2, 1); break;
+    case 211: TQ_DM(2, 1, 1); break;
+    case 212: TQ_DM(2, 1, 2); break;
+    case 214: TQ_DM(2, 1, 4); break;
+    case 221: TQ_DM(2, 2, 1); break;
+    case 222: TQ_DM(2, 2, 2); break;
+    default: TQ_DM(2, 2, 4); break;
   }
 #undef TQ_DM
-#undef TQ_DX
 }
 
 }  // namespace tq

@@ -166,8 +166,8 @@ static tq_status gemv_mx_run(const tq_mat_mx* w, const int8_t* q, const float* d
   if ((int64_t)t * n * (k / 32) > ((int64_t)1 << 40)) return fail(TQ_ERR_INVALID, "tq_gemv_mx: problem too large");
   const int kb = k / 256, nl = (kb + 7) / 8;
   // Several tokens: the matrix cores, except where the matrix is too small to fill them and
-  // one chunk of four tokens does (4 tokens, k = 1024: 4.1 against 4.3 us at 4096 rows, 5.9
-  // against 4.4 at 8192; k = 4096: 4.3 against 5.4 at 2048 rows, 6.0 against 5.6 at 4096).
+  // one chunk of four tokens does (4 tokens, k = 1024: 4.0 us at 4096 rows, where 8192 rows
+  // take 5.9 against 4.4; k = 4096: 4.3 against 5.3 at 2048 rows, 6.1 against 5.4 at 4096).
   if (t > 4 || (t > 1 && (n > 4096 || (int64_t)n * kb > 32768))) {
     (void)hipGetLastError();
     launch_gemv_mfma(2, w->codes, w->scales, n, kb, q, d, (int)t, y, isum_dbg, (hipStream_t)stream, events);
