@@ -1,4 +1,5 @@
-"""Build libtq.so (the HIP library behind include/tq.h) for gfx950 with hipcc, in-tree."""
+"""Build libtq.so (the HIP library behind include/tq.h) for gfx950 with hipcc, and _tqpy.so (the
+native half of the Python binding) with g++, in-tree."""
 from __future__ import annotations
 
 import concurrent.futures as cf
@@ -48,6 +49,24 @@ def build(verbose: bool = False, out: str = LIB, defines=(), obj_dir: str = OBJ)
     return out
 
 
+def build_py() -> str:
+    """Compile the native half of the Python binding (_tqpy.so) against the running torch."""
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    src, out = os.path.join(HERE, "csrc_py", "tq_py.cpp"), os.path.join(HERE, "_tqpy.so")
+    inc = [f"-isystem{p}" for p in [*cpp_extension.include_paths(), sysconfig.get_paths()["include"]]]
+    libs = [f"-L{p}" for p in cpp_extension.library_paths()]
+    tmp = out + ".tmp"
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           *inc, src, "-o", tmp, *libs, "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed for {src}:\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, out)
+    return out
+
+
 def device_asm(src: str) -> str:
     """gfx950 assembly of one source file (for inspection)."""
     out = os.path.join(OBJ, os.path.basename(src) + ".s")
@@ -59,4 +78,5 @@ def device_asm(src: str) -> str:
 
 if __name__ == "__main__":
     build(verbose=True)
+    print(build_py())
     sys.exit(0)

@@ -1,4 +1,5 @@
-"""Python binding of libtq (include/tq.h): argument marshalling only.
+"""Python binding of libtq (include/tq.h): argument marshalling only (a serving loop's calls
+through the native _tqpy.so where it takes their arguments).
 
 Every function here has the name of the C entry point it calls and does no compute of
 its own: it checks dtypes, shapes, devices and contiguity, passes raw pointers and the
@@ -119,6 +120,25 @@ for _name, _args, _res in [
     _f.restype = _res
 
 
+# The native half of the binding (_tqpy.so): checks and call of a serving loop's entry points
+# in one C call. It returns None for arguments that it does not take; the Python path below
+# then runs, and names what is wrong with them.
+try:
+    from . import _tqpy as _fast
+    _fast.bind(*[ctypes.cast(getattr(_L, n), _vp).value for n in (
+        "tq_quantize_act", "tq_gemv", "tq_gemv_f32", "tq_gemv2", "tq_gemv_mx", "tq_moe_grouped")])
+except ImportError:
+    _fast = None
+
+
+def _native(stream) -> bool:
+    return stream is None and _fast is not None and torch.cuda.is_initialized()
+
+
+def _current() -> int:
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
 def tq_last_error() -> str:
     return _L.tq_last_error().decode()
 
@@ -232,6 +252,10 @@ def tq_tied_quantize(w: torch.Tensor, m: TqMatrix, iters: torch.Tensor | None = 
 # -- dot pass -----------------------------------------------------------------------------
 
 def tq_quantize_act(x: torch.Tensor, q: torch.Tensor, d: torch.Tensor, bsum: torch.Tensor, stream=None):
+    if _native(stream):
+        st = _fast.quantize_act(x, q, d, bsum, _current())
+        if st is not None:
+            return _ok(st)
     t, k = x.shape
     _ok(_L.tq_quantize_act(_dev(x, torch.float32, "x"), t, k, _dev(q, torch.int8, "q", (t, k)),
                            _dev(d, torch.float32, "d", (t, k // 256)), _dev(bsum, torch.int32, "bsum", (t, k // 256)),
@@ -240,6 +264,10 @@ def tq_quantize_act(x: torch.Tensor, q: torch.Tensor, d: torch.Tensor, bsum: tor
 
 def tq_gemv(m: TqMatrix, q: torch.Tensor, d: torch.Tensor, bsum: torch.Tensor, y: torch.Tensor,
             isum_dbg: torch.Tensor | None = None, stream=None):
+    if isum_dbg is None and _native(stream):
+        st = _fast.gemv(m.n, m.k, m.codes, m.scales, q, d, bsum, y, _current())
+        if st is not None:
+            return _ok(st)
     t = q.shape[0]
     desc = m.desc()
     dbg = None if isum_dbg is None else _dev(isum_dbg, torch.int32, "isum_dbg", (t, m.n, m.k // 256))
@@ -278,6 +306,10 @@ def tq_gemv_f32(m: TqMatrix, x: torch.Tensor, y: torch.Tensor, q: torch.Tensor, 
                 isum_dbg: torch.Tensor | None = None, stream=None):
     """The dot pass on fp32 activations (quantized in the same launch at one token);
     q, d, bsum receive the quantized activations."""
+    if isum_dbg is None and _native(stream):
+        st = _fast.gemv_f32(m.n, m.k, m.codes, m.scales, x, y, q, d, bsum, _current())
+        if st is not None:
+            return _ok(st)
     _ok(_L.tq_gemv_f32(*_gemv_f32_args(m, x, y, q, d, bsum, isum_dbg), _stream(stream)))
 
 
@@ -354,6 +386,10 @@ def _gemv2_args(m: TqMatrix2, q, d, y, isum_dbg):
 
 def tq_gemv2(m: TqMatrix2, q: torch.Tensor, d: torch.Tensor, y: torch.Tensor, isum_dbg: torch.Tensor | None = None,
              stream=None):
+    if isum_dbg is None and _native(stream):
+        st = _fast.gemv2(m.n, m.k, m.codes, m.scales, q, d, y, _current())
+        if st is not None:
+            return _ok(st)
     _ok(_L.tq_gemv2(*_gemv2_args(m, q, d, y, isum_dbg), _stream(stream)))
 
 
@@ -413,6 +449,10 @@ def _gemv_mx_args(m: TqMatrixMx, q, d, y, isum_dbg):
 
 def tq_gemv_mx(m: TqMatrixMx, q: torch.Tensor, d: torch.Tensor, y: torch.Tensor, isum_dbg: torch.Tensor | None = None,
                stream=None):
+    if isum_dbg is None and _native(stream):
+        st = _fast.gemv_mx(m.n, m.k, m.codes, m.scales, q, d, y, _current())
+        if st is not None:
+            return _ok(st)
     _ok(_L.tq_gemv_mx(*_gemv_mx_args(m, q, d, y, isum_dbg), _stream(stream)))
 
 
@@ -582,6 +622,11 @@ def _moe_args(ex, x, topk_idx, topk_w, out, ws):
 
 
 def tq_moe_grouped(ex: TqExperts, x, topk_idx, topk_w, out, ws, flags: int = 0, stream=None):
+    if _native(stream):
+        st = _fast.moe_grouped(ex.n_experts, ex.hidden, ex.inter, ex.codes, ex.scales, x, topk_idx, topk_w, out, ws, flags,
+                               _current())
+        if st is not None:
+            return _ok(st)
     _ok(_L.tq_moe_grouped(*_moe_args(ex, x, topk_idx, topk_w, out, ws), flags, _stream(stream)))
 
 
