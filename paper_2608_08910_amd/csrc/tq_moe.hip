@@ -109,36 +109,6 @@ static Layout make_layout(int n_experts, int hidden, int inter, int64_t t, int t
 // Shared pieces
 // ---------------------------------------------------------------------------------
 
-// Quantize 8 consecutive 256-blocks per wave of the flattened block grid.
-__device__ __forceinline__ void quantize_wave_blocks(const float* __restrict__ x, int64_t nblocks, int64_t wave_id,
-                                                     int8_t* __restrict__ q, float* __restrict__ d,
-                                                     int32_t* __restrict__ bsum) {
-  const int lane = threadIdx.x & 63;
-  const int64_t blk = wave_id * 8 + (lane >> 3);
-  if (blk >= nblocks) return;
-  const int cp = lane & 7;
-  const float4* xp = reinterpret_cast<const float4*>(x + blk * 256 + cp * 32);
-  float v[32];
-#pragma unroll
-  for (int m = 0; m < 8; ++m) {
-    const float4 f = xp[m];
-    v[4 * m + 0] = f.x;
-    v[4 * m + 1] = f.y;
-    v[4 * m + 2] = f.z;
-    v[4 * m + 3] = f.w;
-  }
-  int qw[8], qs, bs;
-  float dd;
-  quantize_group32(v, qw, qs, dd, bs);
-  int4* qp = reinterpret_cast<int4*>(q + blk * 256 + cp * 32);
-  qp[0] = make_int4(qw[0], qw[1], qw[2], qw[3]);
-  qp[1] = make_int4(qw[4], qw[5], qw[6], qw[7]);
-  if (cp == 0) {
-    d[blk] = dd;
-    bsum[blk] = bs;
-  }
-}
-
 // One matrix of one expert as buffer resources (codes and scales).
 struct MatRsrc {
   __amdgpu_buffer_rsrc_t codes, scales;
@@ -192,20 +162,49 @@ struct MoeArgs {
 // quantization rather than after it) + quantize x (workgroups 1 .. nq)
 // ---------------------------------------------------------------------------------
 
-__global__ __launch_bounds__(256) void k_moe_prologue(const float* __restrict__ x, MoeArgs A) {
+// Inclusive scan over the workgroup's threads (s_w: the waves' totals), with the total: lane
+// exchanges within a wave and one barrier.
+template <int WAVES>
+__device__ __forceinline__ int block_scan(int v, int* s_w, int& total) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int u = __shfl_up(v, off);
+    v += lane >= off ? u : 0;
+  }
+  if (lane == 63) s_w[w] = v;
+  __syncthreads();
+  total = 0;
+#pragma unroll
+  for (int i = 0; i < WAVES; ++i) {
+    const int t = s_w[i];
+    v += i < w ? t : 0;
+    total += t;
+  }
+  return v;
+}
+
+// WAVES: the dispatch workgroup is one serial chain of load, count, rank, scan and place. Four
+// waves up to 4096 slots, whose ids they hold (7.2 us at 32 tokens x top-8, 8.7 with sixteen);
+// sixteen beyond, which hold 16384 in one round trip (2048 tokens x top-8: 18.3 us, where four
+// waves take four round trips, twice: 24.2).
+constexpr int kProSlots = 16;  // ids per thread
+template <int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void k_moe_prologue(const float* __restrict__ x, MoeArgs A) {
+  constexpr int kProWaves = WAVES, kProThreads = WAVES * 64;
   if (blockIdx.x > 0) {
     const int64_t nblocks = A.t * (A.hidden / 256);
-    quantize_wave_blocks(x, nblocks, (int64_t)(blockIdx.x - 1) * 4 + (threadIdx.x >> 6), A.xq, A.xd, A.xb);
+    quantize_wave_blocks(x, nblocks, (int64_t)(blockIdx.x - 1) * kProWaves + (threadIdx.x >> 6), A.xq, A.xd, A.xb);
     return;
   }
   __shared__ int s_cnt[kMaxExperts];   // slots per expert
   __shared__ __attribute__((aligned(16))) int s_base[kMaxExperts];  // rank key, then the slot cursor
   __shared__ int s_ebr[kMaxExperts];   // expert of each rank
-  __shared__ int s_scan[256], s_scan2[256];
+  __shared__ int s_scan[kProWaves], s_scan2[kProWaves];
   __shared__ int s_nact, s_bad, s_tsmall, s_tsingle, s_rhot;
   const int tid = threadIdx.x, E = A.n_experts;
   const int64_t S = A.t * A.topk;
-  for (int e = tid; e < E; e += 256) s_cnt[e] = 0;
+  for (int e = tid; e < E; e += kProThreads) s_cnt[e] = 0;
   if (tid == 0) {
     s_bad = 0;
     s_nact = 0;
@@ -215,20 +214,20 @@ __global__ __launch_bounds__(256) void k_moe_prologue(const float* __restrict__ 
   }
   __syncthreads();
   // The slots' expert ids, kSB per thread at a time, all requested before any is used
-  // (one round trip per batch rather than one per slot); a step of at most 256 * kSB
+  // (one round trip per batch rather than one per slot); a step of at most kProThreads * kSB
   // slots keeps its one batch in registers for the placement pass at the end.
-  constexpr int kSB = 16;
+  constexpr int kSB = kProSlots;
   int ev[kSB];
   const auto load_ids = [&](int64_t s0) {
 #pragma unroll
-    for (int i = 0; i < kSB; ++i) ev[i] = A.topk_idx[min(s0 + tid + 256 * i, S - 1)];
+    for (int i = 0; i < kSB; ++i) ev[i] = A.topk_idx[min(s0 + tid + kProThreads * i, S - 1)];
     __builtin_amdgcn_sched_barrier(0);
   };
-  for (int64_t s0 = 0; s0 < S; s0 += 256 * kSB) {
+  for (int64_t s0 = 0; s0 < S; s0 += kProThreads * kSB) {
     load_ids(s0);
 #pragma unroll
     for (int i = 0; i < kSB; ++i) {
-      if (s0 + tid + 256 * i >= S) continue;
+      if (s0 + tid + kProThreads * i >= S) continue;
       const int e = ev[i];
       if (e >= 0 && e < E) atomicAdd(&s_cnt[e], 1);
       else s_bad = 1;
@@ -246,14 +245,14 @@ __global__ __launch_bounds__(256) void k_moe_prologue(const float* __restrict__ 
     // 0 for an inactive expert. A rank counts the larger keys, four per broadcast LDS
     // read (a loop of dependent single reads costs an LDS round trip per expert).
     const int E4 = (E + 3) & ~3;
-    for (int e = tid; e < E4; e += 256) {
+    for (int e = tid; e < E4; e += kProThreads) {
       const int c = e < E ? s_cnt[e] : 0;
       s_base[e] = c > 0 ? (c << 11) | (2047 - e) : 0;
       if (c > 0) atomicAdd(&s_nact, 1);
     }
     __syncthreads();
     const int4* k4 = reinterpret_cast<const int4*>(s_base);
-    for (int e = tid; e < E; e += 256) {
+    for (int e = tid; e < E; e += kProThreads) {
       const int k = s_base[e];
       if (k == 0) continue;
       int r = 0;
@@ -267,26 +266,19 @@ __global__ __launch_bounds__(256) void k_moe_prologue(const float* __restrict__ 
   } else {
     // an expert's rank is the number of active experts below it: a scan of the active
     // flags over contiguous id ranges
-    const int per = (E + 255) / 256, e0 = min(E, tid * per), e1 = min(E, e0 + per);
+    const int per = (E + kProThreads - 1) / kProThreads, e0 = min(E, tid * per), e1 = min(E, e0 + per);
     int na = 0;
     for (int e = e0; e < e1; ++e) na += s_cnt[e] > 0;
-    s_scan[tid] = na;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-      const int v = tid >= off ? s_scan[tid - off] : 0;
-      __syncthreads();
-      s_scan[tid] += v;
-      __syncthreads();
-    }
-    int r = s_scan[tid] - na;
+    int n_all;
+    int r = block_scan<WAVES>(na, s_scan, n_all) - na;
     for (int e = e0; e < e1; ++e)
       if (s_cnt[e] > 0) s_ebr[r++] = e;
-    if (tid == 255) s_nact = s_scan[255];
+    if (tid == kProThreads - 1) s_nact = n_all;
   }
   __syncthreads();
   const int n_active = s_nact;
   // exclusive scan of the slot counts in rank order, contiguous ranks per thread
-  const int per = (n_active + 255) / 256;
+  const int per = (n_active + kProThreads - 1) / kProThreads;
   const int r0 = min(n_active, tid * per), r1 = min(n_active, r0 + per);
   // (and of the token tiles: kMT-token tiles of every expert for the MFMA path; on the
   // mixed path (t32) instead the kMTs-token tiles of the experts of more than hyb slots,
@@ -298,18 +290,8 @@ __global__ __launch_bounds__(256) void k_moe_prologue(const float* __restrict__ 
     ns += s_cnt[s_ebr[r]];
     nt += ntiles(s_cnt[s_ebr[r]]);
   }
-  s_scan[tid] = ns;
-  s_scan2[tid] = nt;
-  __syncthreads();
-  for (int off = 1; off < 256; off <<= 1) {
-    const int v = tid >= off ? s_scan[tid - off] : 0;
-    const int v2 = tid >= off ? s_scan2[tid - off] : 0;
-    __syncthreads();
-    s_scan[tid] += v;
-    s_scan2[tid] += v2;
-    __syncthreads();
-  }
-  int pos = s_scan[tid] - ns, tpos = s_scan2[tid] - nt;
+  int n_valid, n_tiles;
+  int pos = block_scan<WAVES>(ns, s_scan, n_valid) - ns, tpos = block_scan<WAVES>(nt, s_scan2, n_tiles) - nt;
   for (int r = r0; r < r1; ++r) {
     const int e = s_ebr[r];
     // In count order the experts of at most kMTs slots form the tail of the tile list, the
@@ -334,8 +316,7 @@ __global__ __launch_bounds__(256) void k_moe_prologue(const float* __restrict__ 
     for (const int t1 = tpos + n_t; tpos < t1; ++tpos) te[tpos] = r;
   }
   __syncthreads();
-  if (tid == 255) {
-    const int n_valid = s_scan[255], n_tiles = s_scan2[255];
+  if (tid == kProThreads - 1) {
     const int t_small = min(s_tsmall, n_tiles);
     A.act_off[n_active] = n_valid;
     (t32 ? A.tt32_off : A.tt_off)[n_active] = n_tiles;
@@ -364,11 +345,11 @@ __global__ __launch_bounds__(256) void k_moe_prologue(const float* __restrict__ 
     A.ctrl[kFlags] = s_bad ? 1 : 0;
   }
   __syncthreads();
-  for (int64_t s0 = 0; s0 < S; s0 += 256 * kSB) {
-    if (S > 256 * kSB) load_ids(s0);  // otherwise ev still holds the only batch
+  for (int64_t s0 = 0; s0 < S; s0 += kProThreads * kSB) {
+    if (S > kProThreads * kSB) load_ids(s0);  // otherwise ev still holds the only batch
 #pragma unroll
     for (int i = 0; i < kSB; ++i) {
-      const int64_t s = s0 + tid + 256 * i;
+      const int64_t s = s0 + tid + kProThreads * i;
       if (s >= S) continue;
       const int e = ev[i];
       if (e >= 0 && e < E) {
@@ -1185,38 +1166,13 @@ struct T1Lds {
         b(reinterpret_cast<int*>(raw + kT1LdsQ + (kT1LdsQ / 256) * 4)) {}
 };
 
-// The activation quantizer on 16 lanes per 256-block (16 values a lane, lane (l & 15)
-// holding values 16 (l & 15) .. + 15): the same rule as quantize_group32 (absmax by a
-// butterfly over the 16 lanes, d = amax / 127 and inv = 127 / amax by IEEE division,
-// q = rne(x * inv) by the 1.5 * 2^23 add), written to LDS at block blk; the block's d and
-// code sum go to LDS from its first lane. Half the values a lane of the 8-lane form
-// handles, so the block is ready sooner.
+// 256-block blk quantized on 16 lanes, lane (l & 15) holding values 16 (l & 15) .. + 15, written
+// to LDS at block blk; the block's d and code sum go to LDS from its first lane.
 __device__ __forceinline__ void quantize16_to_lds(const float (&x)[16], int blk, int c16, int8_t* s_q, float* s_d,
                                                   int* s_b, bool store) {
-#pragma clang fp contract(off)
-  float a = 0.0f;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) a = fmaxf(a, fabsf(x[i]));
-  a = group_max_f32(a);
-  a = fmaxf(a, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(a), kDppRowRor8, 0xf, 0xf, false)));
-  int qw[4] = {0, 0, 0, 0};
-  float d = 0.0f;
-  int s = 0;
-  if (a >= 0x1p-100f) {
-    const float inv = 127.0f / a;
-    d = a / 127.0f;
-    constexpr float kMagic = 12582912.0f;  // 1.5 * 2^23
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      uint32_t b[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) b[k] = __float_as_uint(x[4 * m + k] * inv + kMagic);
-      qw[m] = int(__builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u) | __builtin_amdgcn_perm(b[3], b[2], 0x04000c0cu));
-      s = __builtin_amdgcn_sdot4(qw[m], 0x01010101, s, false);
-    }
-  }
-  s = group_sum_i32(s);
-  s += __builtin_amdgcn_update_dpp(0, s, kDppRowRor8, 0xf, 0xf, false);
+  int qw[4], s;
+  float d;
+  quantize_group16(x, qw, d, s);
   if (!store) return;
   *reinterpret_cast<int4*>(s_q + blk * 256 + c16 * 16) = make_int4(qw[0], qw[1], qw[2], qw[3]);
   if (c16 == 0) {
@@ -1865,7 +1821,8 @@ static tq_status moe_run(const tq_experts* ex, const float* x, int64_t t, const 
   const unsigned g_gu = (unsigned)std::min<int64_t>(max_active * A.tiles_gu, cap);
   const unsigned g_dn = (unsigned)std::min<int64_t>(max_active * A.tiles_dn, cap);
   const int64_t xblocks = t * (ex->hidden / 256), hblocks = S * (ex->inter / 256);
-  const int nq = (int)((xblocks + 31) / 32);
+  const int pro_waves = S <= 4 * 64 * kProSlots ? 4 : 16;
+  const int nq = (int)((xblocks + 4 * pro_waves - 1) / (4 * pro_waves));
   hipStream_t stm = (hipStream_t)stream;
 
   (void)hipGetLastError();
@@ -1919,7 +1876,7 @@ static tq_status moe_run(const tq_experts* ex, const float* x, int64_t t, const 
   const int cus8 = std::max(8, device_cus() / 8 * 8);
   const int n_mgus = (int)std::min<int64_t>((max_active * A.tiles_mgus + 7) / 8 * 8, cus8);
   const int n_mdns = (int)std::min<int64_t>((max_active * A.tiles_mdns + 7) / 8 * 8, cus8);
-  if ((st = launch_stage(events, 0, k_moe_prologue, dim3(nq + 1), 256, stm, fn, x, A)) != TQ_OK) return st;
+  if ((st = launch_stage(events, 0, pro_waves == 4 ? k_moe_prologue<4> : k_moe_prologue<16>, dim3(nq + 1), pro_waves * 64, stm, fn, x, A)) != TQ_OK) return st;
   if (mfma && debug)
     st = launch_pair(events, 1, ss, k_moe_mfma<2, kMT, kMWaves, false, true>, dim3(g_mgu), kMWaves * 64,
                        k_moe_mfma<2, kMTs, kMWavesS, true, true>, dim3(g_mgus), kMWavesS * 64, stm, fn, A);
@@ -1934,7 +1891,7 @@ static tq_status moe_run(const tq_experts* ex, const float* x, int64_t t, const 
                      k_moe_mfma<2, kMTs, kMWavesS, true, true, false, true>, dim3(g_mgus), kMWavesS * 64, stm, fn, A);
   else st = launch_stage(events, 1, pick_tb<2>(ex->hidden / 256), dim3(g_gu), kTbWaves * 64, stm, fn, A);
   if (st != TQ_OK) return st;
-  if ((st = launch_stage(events, 2, k_moe_requant, dim3((unsigned)((hblocks + 31) / 32)), 256, stm, fn, A, hblocks)) !=
+  if ((st = launch_stage(events, 2, k_moe_requant, dim3((unsigned)((hblocks + 15) / 16)), 256, stm, fn, A, hblocks)) !=
       TQ_OK)
     return st;
   if (mfma && debug)

@@ -5,42 +5,17 @@
 
 namespace tq {
 
-// One wave quantizes 8 consecutive blocks of the flattened [t][kb] block grid; each
-// 8-lane group owns one block and each lane 32 contiguous values (128 bytes).
 __global__ __launch_bounds__(256) void k_quantize(const float* __restrict__ x, int64_t nblocks,
                                                   int8_t* __restrict__ q, float* __restrict__ d,
                                                   int32_t* __restrict__ bsum) {
-  const int lane = threadIdx.x & 63;
-  const int64_t blk = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 8 + (lane >> 3);
-  if (blk >= nblocks) return;  // uniform across the block's 8-lane group
-  const int cp = lane & 7;
-  const float4* xp = reinterpret_cast<const float4*>(x + blk * 256 + cp * 32);
-  float v[32];
-#pragma unroll
-  for (int m = 0; m < 8; ++m) {
-    const float4 f = xp[m];
-    v[4 * m + 0] = f.x;
-    v[4 * m + 1] = f.y;
-    v[4 * m + 2] = f.z;
-    v[4 * m + 3] = f.w;
-  }
-  int qw[8], qs, bs;
-  float dd;
-  quantize_group32(v, qw, qs, dd, bs);
-  int4* qp = reinterpret_cast<int4*>(q + blk * 256 + cp * 32);
-  qp[0] = make_int4(qw[0], qw[1], qw[2], qw[3]);
-  qp[1] = make_int4(qw[4], qw[5], qw[6], qw[7]);
-  if (cp == 0) {
-    d[blk] = dd;
-    bsum[blk] = bs;
-  }
+  quantize_wave_blocks(x, nblocks, (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6), q, d, bsum);
 }
 
 hipError_t launch_quantize(const float* x, int64_t t, int32_t k, int8_t* q, float* d, int32_t* bsum,
                            hipStream_t st) {
   const int64_t nblocks = t * (k / 256);
   if (nblocks == 0) return hipSuccess;
-  const int64_t wgs = (nblocks + 31) / 32;
+  const int64_t wgs = (nblocks + 15) / 16;
   hipLaunchKernelGGL(k_quantize, dim3((unsigned)wgs), dim3(256), 0, st, x, nblocks, q, d, bsum);
   return hipSuccess;
 }
