@@ -504,7 +504,7 @@ def run_twoplane(args, wl, cfg):
                              "two_plane_GBps": round((two_plane_bytes(n, k) + t * (k + kb * 4 + n * 4)) / (m2 * 1e-3) / 1e9, 1),
                              "folded_GBps": round((matrix_bytes(n, k) + t * (k + kb * 4 + n * 4)) / (mf * 1e-3) / 1e9, 1)}
     ms = by_tokens["1"]["two_plane_ms"]
-    roof = hbm_roof("gemv2", two_plane_bytes(n, k) + k + kb * 4 + n * 4, ms, "k_gemv2<2, 1, 4, false>")
+    roof = hbm_roof("gemv2", two_plane_bytes(n, k) + k + kb * 4 + n * 4, ms, "k_gemv2<2, 1, 4>")
     return dict(value=gbs, K=K, W=W, elapsed=elapsed, reps=reps, tokens=K, roof=roof,
                 config={"workload": cfg["name"], "n": n, "k": k, "tokens_per_step": 1, "bits_per_weight": 4.125,
                         "rotating_copies": copies, "format": "free-scale two-plane (2 x 2-bit trit planes, 2 f16 scales "

@@ -19,7 +19,7 @@
 
 namespace tq {
 
-// One chunk of at most NT tokens (t <= NT).
+// One chunk of at most NT tokens (blockIdx.y: which).
 template <int NL, int NT, int RPW>
 __global__ __launch_bounds__(256) void k_gemv(const uint8_t* __restrict__ codes,
                                               const uint16_t* __restrict__ scales, int n, int kb,
@@ -33,6 +33,12 @@ __global__ __launch_bounds__(256) void k_gemv(const uint8_t* __restrict__ codes,
   const int row0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * RPW;
   if (row0 >= n) return;
   const int64_t k = (int64_t)kb * 256;
+  const int64_t c0 = (int64_t)blockIdx.y * NT;
+  q += c0 * k;
+  d += c0 * kb;
+  y += c0 * n;
+  if (isum_dbg != nullptr) isum_dbg += c0 * n * kb;
+  t -= (int)c0;
 
   // The activations and block scales are requested before the weights: a compute unit
   // returns loads in issue order, so these small, cache-resident loads would otherwise wait
@@ -277,26 +283,29 @@ static tq_status gemv_run(const tq_mat* w, const int8_t* q, const float* d, cons
     return fail(TQ_ERR_ALIGN, "tq_gemv: q must be 16-byte aligned, other buffers naturally aligned");
   if ((int64_t)t * n * (k / 256) > ((int64_t)1 << 40)) return fail(TQ_ERR_INVALID, "tq_gemv: problem too large");
   const int kb = k / 256, nl = (kb + 7) / 8;
-  // Several tokens: the matrix cores, except where the matrix is too small to fill them and
-  // one chunk of four tokens does (4 tokens, k = 4096: 3.95 against 4.25 us at 2048 rows,
-  // 5.48 against 4.47 at 4096; k = 16384: 6.1 against 8.1 at 512 rows, 11.6 against 8.4 at 2048).
-  if (t > 4 || (t > 1 && (n > 2048 || (int64_t)n * kb > 65536))) {
+  const int nt = t == 1 ? 1 : 4;
+  const unsigned chunks = (unsigned)((t + nt - 1) / nt);
+  // Several tokens: the matrix cores, except where the VALU chunks' wave loads (1 KB each, of
+  // four tokens) are too few to fill the chip and launch latency decides (k = 4096, us VALU against MFMA:
+  // 1500 rows, 4 tokens 4.0 / 4.4, 8 tokens 4.8 / 4.4; 700 rows, 8 tokens 4.0 / 4.3, 16 tokens 4.9 / 4.5;
+  // k = 256: 700 rows, 16 tokens 3.3 / 3.6, 1500 rows 4.1 / 3.8; k = 12544: 700 rows, 4 tokens 5.7 / 7.1,
+  // 8 tokens 10.1 / 7.2).
+  if (t > 16 || (t > 1 && (int64_t)n * chunks * nt * nl > 4 * (nl > 2 ? 5600 : 3800))) {
     (void)hipGetLastError();
     launch_gemv_mfma(0, w->codes, w->scales, n, kb, q, d, (int)t, y, isum_dbg, (hipStream_t)stream, events);
     return check_launch("tq_gemv");
   }
-  const int nt = t == 1 ? 1 : 4;
   // Few rows: one row per wave, to spread a small matrix over all CUs.
-  const int rpw = (n >= 16384 && nl <= 2) ? 4 : 1;
+  const int rpw = (t == 1 && n >= 16384 && nl <= 2) ? 4 : 1;
   const int64_t waves = (n + rpw - 1) / rpw;
   const unsigned wgs = (unsigned)((waves + 3) / 4);
   (void)hipGetLastError();
   if (events)
-    hipExtLaunchKernelGGL(pick_gemv(nl, nt, rpw), dim3(wgs), dim3(256), 0, (hipStream_t)stream, (hipEvent_t)events[0],
-                          (hipEvent_t)events[1], 0, w->codes, w->scales, n, kb, q, d, (int)t, y, isum_dbg);
+    hipExtLaunchKernelGGL(pick_gemv(nl, nt, rpw), dim3(wgs, chunks), dim3(256), 0, (hipStream_t)stream,
+                          (hipEvent_t)events[0], (hipEvent_t)events[1], 0, w->codes, w->scales, n, kb, q, d, (int)t, y, isum_dbg);
   else
-    hipLaunchKernelGGL(pick_gemv(nl, nt, rpw), dim3(wgs), dim3(256), 0, (hipStream_t)stream, w->codes, w->scales, n,
-                       kb, q, d, (int)t, y, isum_dbg);
+    hipLaunchKernelGGL(pick_gemv(nl, nt, rpw), dim3(wgs, chunks), dim3(256), 0, (hipStream_t)stream, w->codes, w->scales,
+                       n, kb, q, d, (int)t, y, isum_dbg);
   return check_launch("tq_gemv");
 }
 }  // namespace tq

@@ -34,9 +34,8 @@ __device__ __forceinline__ void dot2_chunk16(const uint4 w, const int (&a)[8], i
   p2 = s2;
 }
 
-// LOOP = false: one chunk of at most NT tokens (t <= NT), no token loop, so nothing
-// loop-invariant (the unpacked planes) is hoisted and kept live across it.
-template <int NL, int NT, int RPW, bool LOOP>
+// One chunk of at most NT tokens (blockIdx.y: which).
+template <int NL, int NT, int RPW>
 __global__ __launch_bounds__(256) void k_gemv2(const uint8_t* __restrict__ codes,
                                                const uint32_t* __restrict__ scales, int n, int kb,
                                                const int8_t* __restrict__ q, const float* __restrict__ d, int t,
@@ -50,36 +49,39 @@ __global__ __launch_bounds__(256) void k_gemv2(const uint8_t* __restrict__ codes
   const int row0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * RPW;
   if (row0 >= n) return;
   const int64_t k = (int64_t)kb * 256;
+  const int64_t c0 = (int64_t)blockIdx.y * NT;
+  q += c0 * k;
+  d += c0 * kb;
+  y += c0 * n;
+  if (isum_dbg != nullptr) isum_dbg += c0 * n * kb * 2;
+  t -= (int)c0;
 
-  // The activations and block scales of a chunk of NT tokens. The first chunk's are
-  // requested before the weights: a compute unit returns loads in issue order, so these
-  // small, cache-resident loads would otherwise wait behind every weight load in flight.
+  // The activations and block scales are requested before the weights: a compute unit
+  // returns loads in issue order, so these small, cache-resident loads would otherwise wait
+  // behind every weight load in flight.
   int qa[NT][NL][8];
   float dk[KI][NL];
-  auto load_acts = [&](int t0) {
 #pragma unroll
-    for (int tt = 0; tt < NT; ++tt)
+  for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
-      for (int i = 0; i < NL; ++i) {
-        const int64_t tc = min(t0 + tt, t - 1);
-        const int4* p = reinterpret_cast<const int4*>(q + tc * k + min(8 * i + g, kb - 1) * 256 + cp * 32);
-        const int4 lo = p[0], hi = p[1];
-        qa[tt][i][0] = lo.x; qa[tt][i][1] = lo.y; qa[tt][i][2] = lo.z; qa[tt][i][3] = lo.w;
-        qa[tt][i][4] = hi.x; qa[tt][i][5] = hi.y; qa[tt][i][6] = hi.z; qa[tt][i][7] = hi.w;
-      }
-    // the lane's kept items: their tokens' block scales (masked at use: a select here
-    // would make the compiler wait for these loads before issuing the weights)
-#pragma unroll
-    for (int kk = 0; kk < KI; ++kk) {
-      const int tok = t0 + RI::kept(kk, lane) % NT;
-#pragma unroll
-      for (int i = 0; i < NL; ++i) {
-        const int b = 8 * i + g;
-        dk[kk][i] = d[(int64_t)min(tok, t - 1) * kb + min(b, kb - 1)];
-      }
+    for (int i = 0; i < NL; ++i) {
+      const int64_t tc = min(tt, t - 1);
+      const int4* p = reinterpret_cast<const int4*>(q + tc * k + min(8 * i + g, kb - 1) * 256 + cp * 32);
+      const int4 lo = p[0], hi = p[1];
+      qa[tt][i][0] = lo.x; qa[tt][i][1] = lo.y; qa[tt][i][2] = lo.z; qa[tt][i][3] = lo.w;
+      qa[tt][i][4] = hi.x; qa[tt][i][5] = hi.y; qa[tt][i][6] = hi.z; qa[tt][i][7] = hi.w;
     }
-  };
-  load_acts(0);
+  // the lane's kept items: their tokens' block scales (masked at use: a select here
+  // would make the compiler wait for these loads before issuing the weights)
+#pragma unroll
+  for (int kk = 0; kk < KI; ++kk) {
+    const int tok = RI::kept(kk, lane) % NT;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int b = 8 * i + g;
+      dk[kk][i] = d[(int64_t)min(tok, t - 1) * kb + min(b, kb - 1)];
+    }
+  }
 
   // Loads are unconditional from clamped addresses (a predicated load becomes a branch
   // that serializes the loads): rows past n are computed and not stored, blocks past kb
@@ -107,75 +109,65 @@ __global__ __launch_bounds__(256) void k_gemv2(const uint8_t* __restrict__ codes
 
   __builtin_amdgcn_sched_barrier(0);  // every load above is issued before any math
 
-  // t >= 1 (the launcher returns early for t == 0): a do-while keeps the loads above
-  // in the kernel's entry block instead of sinking them under a loop guard
-  int t0 = 0;
-  do {
-    if (t0 > 0) load_acts(t0);
-    float acc[KI];
+  float acc[KI];
 #pragma unroll
-    for (int kk = 0; kk < KI; ++kk) acc[kk] = 0.0f;
+  for (int kk = 0; kk < KI; ++kk) acc[kk] = 0.0f;
 #pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      int p[RPW * NT * 2];
+  for (int i = 0; i < NL; ++i) {
+    int p[RPW * NT * 2];
 #pragma unroll
-      for (int r = 0; r < RPW; ++r)
+    for (int r = 0; r < RPW; ++r)
 #pragma unroll
-        for (int tt = 0; tt < NT; ++tt) dot2_chunk16(w[r][i], qa[tt][i], p[(r * NT + tt) * 2], p[(r * NT + tt) * 2 + 1]);
-      RI::block_sums(p);
+      for (int tt = 0; tt < NT; ++tt) dot2_chunk16(w[r][i], qa[tt][i], p[(r * NT + tt) * 2], p[(r * NT + tt) * 2 + 1]);
+    RI::block_sums(p);
 #pragma unroll
-      for (int kk = 0; kk < KI; ++kk) {
-        const int is1 = p[2 * kk] >> 6, is2 = p[2 * kk + 1] >> 6;  // exact block sums per plane
-        const int tok = t0 + RI::kept(kk, lane) % NT, b = 8 * i + g;
-        const float dv = (tok < t && b < kb) ? dk[kk][i] : 0.0f;
-        acc[kk] = fmaf(a1[i] * dv, (float)is1, acc[kk]);
-        acc[kk] = fmaf(a2[i] * dv, (float)is2, acc[kk]);
-        if (isum_dbg != nullptr && RI::block_writer(lane)) {
-          const int row = row0 + RI::kept(kk, lane) / NT;
-          if (tok < t && row < n && b < kb) {
-            int32_t* o = isum_dbg + (((int64_t)tok * n + row) * kb + b) * 2;
-            o[0] = is1;
-            o[1] = is2;
-          }
+    for (int kk = 0; kk < KI; ++kk) {
+      const int is1 = p[2 * kk] >> 6, is2 = p[2 * kk + 1] >> 6;  // exact block sums per plane
+      const int tok = RI::kept(kk, lane) % NT, b = 8 * i + g;
+      const float dv = (tok < t && b < kb) ? dk[kk][i] : 0.0f;
+      acc[kk] = fmaf(a1[i] * dv, (float)is1, acc[kk]);
+      acc[kk] = fmaf(a2[i] * dv, (float)is2, acc[kk]);
+      if (isum_dbg != nullptr && RI::block_writer(lane)) {
+        const int row = row0 + RI::kept(kk, lane) / NT;
+        if (tok < t && row < n && b < kb) {
+          int32_t* o = isum_dbg + (((int64_t)tok * n + row) * kb + b) * 2;
+          o[0] = is1;
+          o[1] = is2;
         }
       }
     }
-    RF::block_totals(acc);
-    if (RF::writer(lane)) {
-      const int it = RF::item(lane), tok = t0 + it % NT, row = row0 + it / NT;
-      if (tok < t && row < n) y[(int64_t)tok * n + row] = acc[0];
-    }
-    t0 += NT;
-  } while (LOOP && t0 < t);
+  }
+  RF::block_totals(acc);
+  if (RF::writer(lane)) {
+    const int it = RF::item(lane), tok = it % NT, row = row0 + it / NT;
+    if (tok < t && row < n) y[(int64_t)tok * n + row] = acc[0];
+  }
 }
 
 using gemv2_fn = void (*)(const uint8_t*, const uint32_t*, int, int, const int8_t*, const float*, int, float*,
                           int32_t*);
 
 // Register budget: four rows per wave only for one token where a row is at most two loads,
-// four tokens at once only where a row is at most four loads (longer rows walk them).
+// four tokens at once only where a row is at most four loads.
 template <int NL>
-static gemv2_fn pick_gemv2_nl(int nt, int rpw, bool one) {
-  if constexpr (NL <= 4) {
-    if (nt == 4) return k_gemv2<NL, 4, 1, false>;
-    if constexpr (NL <= 2)
-      if (rpw == 4) return k_gemv2<NL, 1, 4, false>;
-    return k_gemv2<NL, 1, 1, false>;
-  } else {
-    return one ? k_gemv2<NL, 1, 1, false> : k_gemv2<NL, 1, 1, true>;
-  }
+static gemv2_fn pick_gemv2_nl(int nt, int rpw) {
+  if constexpr (NL <= 4)
+    if (nt == 4) return k_gemv2<NL, 4, 1>;
+  if constexpr (NL <= 2)
+    if (rpw == 4) return k_gemv2<NL, 1, 4>;
+  return k_gemv2<NL, 1, 1>;
 }
 
-static gemv2_fn pick_gemv2(int nl, int nt, int rpw, bool one) {
+static gemv2_fn pick_gemv2(int nl, int nt, int rpw) {
   switch (nl) {
-    case 1: return pick_gemv2_nl<1>(nt, rpw, one);
-    case 2: return pick_gemv2_nl<2>(nt, rpw, one);
-    case 3: return pick_gemv2_nl<3>(nt, rpw, one);
-    case 4: return pick_gemv2_nl<4>(nt, rpw, one);
-    case 5: return pick_gemv2_nl<5>(nt, rpw, one);
-    case 6: return pick_gemv2_nl<6>(nt, rpw, one);
-    case 7: return pick_gemv2_nl<7>(nt, rpw, one);
-    default: return pick_gemv2_nl<8>(nt, rpw, one);
+    case 1: return pick_gemv2_nl<1>(nt, rpw);
+    case 2: return pick_gemv2_nl<2>(nt, rpw);
+    case 3: return pick_gemv2_nl<3>(nt, rpw);
+    case 4: return pick_gemv2_nl<4>(nt, rpw);
+    case 5: return pick_gemv2_nl<5>(nt, rpw);
+    case 6: return pick_gemv2_nl<6>(nt, rpw);
+    case 7: return pick_gemv2_nl<7>(nt, rpw);
+    default: return pick_gemv2_nl<8>(nt, rpw);
   }
 }
 
@@ -195,26 +187,28 @@ static tq_status gemv2_run(const tq_mat2* w, const int8_t* q, const float* d, in
     return fail(TQ_ERR_ALIGN, "tq_gemv2: q must be 16-byte and scales 4-byte aligned, other buffers naturally aligned");
   if ((int64_t)t * n * (k / 256) > ((int64_t)1 << 39)) return fail(TQ_ERR_INVALID, "tq_gemv2: problem too large");
   const int kb = k / 256, nl = (kb + 7) / 8;
-  // Several tokens: the matrix cores, except where the matrix is too small to fill them and
-  // one chunk of four tokens does (4 tokens, k = 4096: 4.20 against 4.30 us at 2048 rows,
-  // 5.94 against 4.44 at 4096; k = 16384, 2 tokens: 5.7 against 8.0 at 512 rows, 10.9 against 8.5 at 2048).
-  if (t > 4 || (t > 1 && (n > 2048 || (int64_t)n * kb > 65536))) {
+  const int nt = (t == 1 || nl > 4) ? 1 : 4;
+  const unsigned chunks = (unsigned)((t + nt - 1) / nt);
+  // Several tokens: the matrix cores, except where the VALU chunks' wave loads (1 KB each, of
+  // four tokens) are too few to fill the chip and launch latency decides (k = 4096, us VALU against MFMA:
+  // 700 rows, 4 tokens 3.5 / 4.3, 8 tokens 4.3 / 4.3, 16 tokens 5.3 / 4.6; k = 1024: 1500 rows, 4 tokens
+  // 3.3 / 3.6, 8 tokens 3.7 / 3.6; k = 12544: 300 rows, 4 tokens 5.6 / 7.0, 8 tokens 7.3 / 7.2).
+  if (t > 16 || (t > 1 && (int64_t)n * chunks * nt * nl > 4 * 3000)) {
     (void)hipGetLastError();
     launch_gemv_mfma(1, w->codes, w->scales, n, kb, q, d, (int)t, y, isum_dbg, (hipStream_t)stream, events);
     return check_launch("tq_gemv2");
   }
-  const int nt = (t == 1 || nl > 4) ? 1 : 4;
-  const int rpw = (n >= 16384 && nl <= 2) ? 4 : 1;
+  const int rpw = (t == 1 && n >= 16384 && nl <= 2) ? 4 : 1;
   const int64_t waves = (n + rpw - 1) / rpw;
   const unsigned wgs = (unsigned)((waves + 3) / 4);
   const uint32_t* sc = reinterpret_cast<const uint32_t*>(w->scales);
   (void)hipGetLastError();
   if (events)
-    hipExtLaunchKernelGGL(pick_gemv2(nl, nt, rpw, t == 1), dim3(wgs), dim3(256), 0, (hipStream_t)stream,
+    hipExtLaunchKernelGGL(pick_gemv2(nl, nt, rpw), dim3(wgs, chunks), dim3(256), 0, (hipStream_t)stream,
                           (hipEvent_t)events[0], (hipEvent_t)events[1], 0, w->codes, sc, n, kb, q, d, (int)t, y,
                           isum_dbg);
   else
-    hipLaunchKernelGGL(pick_gemv2(nl, nt, rpw, t == 1), dim3(wgs), dim3(256), 0, (hipStream_t)stream, w->codes, sc, n, kb, q,
+    hipLaunchKernelGGL(pick_gemv2(nl, nt, rpw), dim3(wgs, chunks), dim3(256), 0, (hipStream_t)stream, w->codes, sc, n, kb, q,
                        d, (int)t, y, isum_dbg);
   return check_launch("tq_gemv2");
 }

@@ -32,7 +32,7 @@ __device__ __forceinline__ int mx_dot32(const uint4 w, const int (&a)[8]) {
   return acc;
 }
 
-// One chunk of at most NT tokens (t <= NT; more tokens: tq_gemv_mfma.hip).
+// One chunk of at most NT tokens (blockIdx.y: which; more tokens: tq_gemv_mfma.hip).
 template <int NL, int NT, int RPW>
 __global__ __launch_bounds__(256) void k_gemv_mx(const uint8_t* __restrict__ codes, const uint8_t* __restrict__ scales,
                                                  int n, int kb, const int8_t* __restrict__ q,
@@ -47,6 +47,12 @@ __global__ __launch_bounds__(256) void k_gemv_mx(const uint8_t* __restrict__ cod
   const int row0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * RPW;
   if (row0 >= n) return;
   const int64_t k = (int64_t)kb * 256;
+  const int64_t c0 = (int64_t)blockIdx.y * NT;
+  q += c0 * k;
+  d += c0 * kb;
+  y += c0 * n;
+  if (isum_dbg != nullptr) isum_dbg += c0 * n * (kb * 8);
+  t -= (int)c0;
 
   // The activations and block scales, requested before the weights (a compute unit returns
   // loads in issue order).
@@ -165,27 +171,29 @@ static tq_status gemv_mx_run(const tq_mat_mx* w, const int8_t* q, const float* d
     return fail(TQ_ERR_ALIGN, "tq_gemv_mx: q must be 16-byte aligned, other buffers naturally aligned");
   if ((int64_t)t * n * (k / 32) > ((int64_t)1 << 40)) return fail(TQ_ERR_INVALID, "tq_gemv_mx: problem too large");
   const int kb = k / 256, nl = (kb + 7) / 8;
-  // Several tokens: the matrix cores, except where the matrix is too small to fill them and
-  // one chunk of four tokens does (4 tokens, k = 1024: 4.0 us at 4096 rows, where 8192 rows
-  // take 5.9 against 4.4; k = 4096: 4.3 against 5.3 at 2048 rows, 6.1 against 5.4 at 4096).
-  if (t > 4 || (t > 1 && (n > 4096 || (int64_t)n * kb > 32768))) {
+  const int nt = t == 1 ? 1 : 4;
+  const unsigned chunks = (unsigned)((t + nt - 1) / nt);
+  // Several tokens: the matrix cores, except where the VALU chunks' wave loads (1 KB each, of
+  // four tokens) are too few to fill the chip and launch latency decides (k = 4096, us VALU against MFMA:
+  // 1500 rows, 4 tokens 4.4 / 5.3, 8 tokens 5.3 / 5.3, 16 tokens 8.1 / 5.5; k = 256: 3000 rows, 4 tokens
+  // 3.4 / 4.1, 8 tokens 4.5 / 4.3; k = 12544: 700 rows, 4 tokens 6.6 / 9.2, 8 tokens 12.0 / 9.2).
+  if (t > 16 || (t > 1 && (int64_t)n * chunks * nt * nl > 4 * (nl > 2 ? 6400 : 4800))) {
     (void)hipGetLastError();
     launch_gemv_mfma(2, w->codes, w->scales, n, kb, q, d, (int)t, y, isum_dbg, (hipStream_t)stream, events);
     return check_launch("tq_gemv_mx");
   }
-  const int nt = t == 1 ? 1 : 4;
   // (one token, large matrix: 2 rows per wave measured best: the table decode makes a wave's
   // compute long enough that four rows lengthen the tail)
-  const int rpw = (n >= 16384 && nl <= 2) ? 2 : 1;
+  const int rpw = (t == 1 && n >= 16384 && nl <= 2) ? 2 : 1;
   const int64_t waves = (n + rpw - 1) / rpw;
   const unsigned wgs = (unsigned)((waves + 3) / 4);
   (void)hipGetLastError();
   if (events)
-    hipExtLaunchKernelGGL(pick_gemv_mx(nl, nt, rpw), dim3(wgs), dim3(256), 0, (hipStream_t)stream,
+    hipExtLaunchKernelGGL(pick_gemv_mx(nl, nt, rpw), dim3(wgs, chunks), dim3(256), 0, (hipStream_t)stream,
                           (hipEvent_t)events[0], (hipEvent_t)events[1], 0, w->codes, w->scales, n, kb, q, d, (int)t, y,
                           isum_dbg);
   else
-    hipLaunchKernelGGL(pick_gemv_mx(nl, nt, rpw), dim3(wgs), dim3(256), 0, (hipStream_t)stream, w->codes, w->scales,
+    hipLaunchKernelGGL(pick_gemv_mx(nl, nt, rpw), dim3(wgs, chunks), dim3(256), 0, (hipStream_t)stream, w->codes, w->scales,
                        n, kb, q, d, (int)t, y, isum_dbg);
   return check_launch("tq_gemv_mx");
 }
