@@ -131,8 +131,9 @@ except ImportError:
     _fast = None
 
 
-def _native(stream) -> bool:
-    return stream is None and _fast is not None and torch.cuda.is_initialized()
+def _native(stream, weights=None, cls=None) -> bool:
+    # (a weights object of another class describes itself by its own desc())
+    return stream is None and _fast is not None and type(weights) is (cls or type(None)) and torch.cuda.is_initialized()
 
 
 def _current() -> int:
@@ -264,7 +265,7 @@ def tq_quantize_act(x: torch.Tensor, q: torch.Tensor, d: torch.Tensor, bsum: tor
 
 def tq_gemv(m: TqMatrix, q: torch.Tensor, d: torch.Tensor, bsum: torch.Tensor, y: torch.Tensor,
             isum_dbg: torch.Tensor | None = None, stream=None):
-    if isum_dbg is None and _native(stream):
+    if isum_dbg is None and _native(stream, m, TqMatrix):
         st = _fast.gemv(m.n, m.k, m.codes, m.scales, q, d, bsum, y, _current())
         if st is not None:
             return _ok(st)
@@ -306,7 +307,7 @@ def tq_gemv_f32(m: TqMatrix, x: torch.Tensor, y: torch.Tensor, q: torch.Tensor, 
                 isum_dbg: torch.Tensor | None = None, stream=None):
     """The dot pass on fp32 activations (quantized in the same launch at one token);
     q, d, bsum receive the quantized activations."""
-    if isum_dbg is None and _native(stream):
+    if isum_dbg is None and _native(stream, m, TqMatrix):
         st = _fast.gemv_f32(m.n, m.k, m.codes, m.scales, x, y, q, d, bsum, _current())
         if st is not None:
             return _ok(st)
@@ -386,7 +387,7 @@ def _gemv2_args(m: TqMatrix2, q, d, y, isum_dbg):
 
 def tq_gemv2(m: TqMatrix2, q: torch.Tensor, d: torch.Tensor, y: torch.Tensor, isum_dbg: torch.Tensor | None = None,
              stream=None):
-    if isum_dbg is None and _native(stream):
+    if isum_dbg is None and _native(stream, m, TqMatrix2):
         st = _fast.gemv2(m.n, m.k, m.codes, m.scales, q, d, y, _current())
         if st is not None:
             return _ok(st)
@@ -449,7 +450,7 @@ def _gemv_mx_args(m: TqMatrixMx, q, d, y, isum_dbg):
 
 def tq_gemv_mx(m: TqMatrixMx, q: torch.Tensor, d: torch.Tensor, y: torch.Tensor, isum_dbg: torch.Tensor | None = None,
                stream=None):
-    if isum_dbg is None and _native(stream):
+    if isum_dbg is None and _native(stream, m, TqMatrixMx):
         st = _fast.gemv_mx(m.n, m.k, m.codes, m.scales, q, d, y, _current())
         if st is not None:
             return _ok(st)
@@ -622,7 +623,7 @@ def _moe_args(ex, x, topk_idx, topk_w, out, ws):
 
 
 def tq_moe_grouped(ex: TqExperts, x, topk_idx, topk_w, out, ws, flags: int = 0, stream=None):
-    if _native(stream):
+    if _native(stream, ex, TqExperts):
         st = _fast.moe_grouped(ex.n_experts, ex.hidden, ex.inter, ex.codes, ex.scales, x, topk_idx, topk_w, out, ws, flags,
                                _current())
         if st is not None:

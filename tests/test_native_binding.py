@@ -25,6 +25,14 @@ def test_native_functions_leave_what_they_do_not_take():
         tq.tq_quantize_act(x, q, d, b)
 
 
+def test_weights_objects_that_describe_themselves_keep_the_python_path(monkeypatch):
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    m = tq.TqMatrix(1, 256, None, None)
+    assert tq._native(None, m, tq.TqMatrix) and tq._native(None) and not tq._native(0, m, tq.TqMatrix)
+    assert not tq._native(None, type("Own", (tq.TqMatrix,), {})(1, 256, None, None), tq.TqMatrix)
+    assert not tq._native(None, tq.TqExpertRecords(1, 256, 256, None), tq.TqExperts)
+
+
 GPU_CALLS = ["quantize_act", "gemv", "gemv_f32", "gemv2", "gemv_mx"]
 
 
