@@ -67,12 +67,16 @@ __device__ __forceinline__ void wait_vmcnt() {
 // MXFP4 on the scaled fp8 x fp4 MFMA. The released bytes are its fp4 operand as they are: a
 // lane's 16-byte chunk is 32 codes with their own e8m0 scale. The int8 activations go in as
 // two fp8 (e4m3) operands, q = 16 h + l with l = q & 15 and h = q >> 4: both at most four
-// significant bits, so exact, as is every product, and the unit adds them in fp32, without
-// rounding while a row block's scales span at most 2^8 (short of extreme codes and activations
-// throughout); measured against 64 bits: 5.0e-8 to 5.7e-8 of the result's norm, 6.8e-8 to
-// 7.4e-8 from whole-number sums scaled chunk by chunk. A wave with a wider span takes those.
-// They need a decode of every code and a scaling of every 32-element sum: 32768 x 4096, 4 tokens: 21 us, 28 so (VALU pass
-// 38.4); 2048 x 4096, 509 tokens: 25 us, 49 so (VALU pass 151).
+// significant bits, so exact, as is every product. Each has its own fp32 accumulator: a block's
+// low halves add up to at most 256 x 15 x 12 (doubled codes, < 2^15.5) and its high halves to
+// 256 x 8 x 12, in units of half the block's least scale; while the row block's scales span at
+// most 2^8, every partial sum is below 2^24 of these units, so both come out exact whatever the
+// unit's order, and their sum is rounded once. (One accumulator for both would keep that only to
+// a span of 2^5.) A row block of a wider span takes whole-number sums chunk by chunk, scaled one
+// by one: they need a decode of every code and a scaling of every 32-element sum (32768 x 4096,
+// 4 tokens: 20.4 us, 37.5 so, VALU pass 38.2; 2048 x 4096, 509 tokens: 25.8 us, 49 so, VALU pass
+// 151). Against 64 bits: 5.0e-8 to 5.7e-8 of the result's norm, 6.8e-8 to 7.4e-8 from whole-number
+// sums scaled chunk by chunk.
 // ---------------------------------------------------------------------------------
 
 typedef int v8i __attribute__((ext_vector_type(8)));
@@ -266,9 +270,9 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
       wave_lds_fence();
       __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));  // LDS reads done: the area may be refilled
       wave_lds_fence();
-      // MXFP4: the block's scales, and whether a row's span more than 2^8 (its fp32 sums could
-      // then round where the whole-number sums do not) or any is outside 2^+-63 (they could
-      // overflow, or lose bits that d brings back). Halves: E and 255 - E, maxima over the
+      // MXFP4: the block's scales, and whether a row's span more than 2^8 (the unit's sums need
+      // not be exact then) or any is outside 2^+-63 (they could overflow, or lose bits that d
+      // brings back). Halves: E and 255 - E, maxima over the
       // row's eight chunks.
       uint32_t es[MX ? RT : 1][2];
       if constexpr (MX) {
@@ -318,25 +322,25 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
 #pragma unroll
           for (int rt = 0; rt < RT; ++rt) {
             if (rt + 1 < RT) stage_w(rt + 1);
-            v4f C[MTT];
+            v4f Cl[MTT], Ch[MTT];  // each exact
 #pragma unroll
-            for (int mt = 0; mt < MTT; ++mt) C[mt] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+            for (int mt = 0; mt < MTT; ++mt) Cl[mt] = Ch[mt] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
               const uint4 w = wt[rt & 1][c];
               const v8i bw = {(int)w.x, (int)w.y, (int)w.z, (int)w.w, 0, 0, 0, 0};
 #pragma unroll
               for (int mt = 0; mt < MTT; ++mt)
-                C[mt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(alo[mt][c], bw, C[mt], 0, 4, 0, kLoScale, 0, (int)es[rt][c]);
+                Cl[mt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(alo[mt][c], bw, Cl[mt], 0, 4, 0, kLoScale, 0, (int)es[rt][c]);
 #pragma unroll
               for (int mt = 0; mt < MTT; ++mt)
-                C[mt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ahi[mt][c], bw, C[mt], 0, 4, 0, kHiScale, 0, (int)es[rt][c]);
+                Ch[mt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ahi[mt][c], bw, Ch[mt], 0, 4, 0, kHiScale, 0, (int)es[rt][c]);
             }
 #pragma unroll
             for (int mt = 0; mt < MTT; ++mt) {
               const float dv[4] = {d4[mt].x, d4[mt].y, d4[mt].z, d4[mt].w};
 #pragma unroll
-              for (int v = 0; v < 4; ++v) acc[mt][rt][v] = fmaf(dv[v], C[mt][v], acc[mt][rt][v]);
+              for (int v = 0; v < 4; ++v) acc[mt][rt][v] = fmaf(dv[v], Cl[mt][v] + Ch[mt][v], acc[mt][rt][v]);
             }
           }
         }

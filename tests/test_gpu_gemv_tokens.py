@@ -101,3 +101,63 @@ def test_mx_scale_range(tq, oracle, n, k, t, e_lo, e_hi):
     y = torch.full((t, n), float("nan"), device="cuda")
     call(q, d, y, None)
     check_mx_tokens(tq, oracle, m, q, d, y)
+
+
+# -- MXFP4 on the scaled matrix unit ---------------------------------------------------------
+# sizes that the launcher gives each of its tiles (16-token x 16-row tiles, rows of five blocks
+# or more): ragged last row tile, ragged tokens
+MX_TILES = {"1x1": (4107, 5), "1x2": (8205, 9), "1x4": (16397, 16), "2x1": (4107, 19), "2x2": (8205, 31), "2x4": (16397, 20)}
+DOUBLED = torch.tensor([0, 1, 2, 3, 4, 6, 8, 12, 0, -1, -2, -3, -4, -6, -8, -12], dtype=torch.float64)
+
+
+def mx_exact(c4, e8, q, blocks):
+    """fp64 (exact: whole numbers below 2^28 times a power of two) sums of block blocks[t] of token t: [t][n]."""
+    n, k = c4.shape
+    w = DOUBLED.cuda()[c4.long()].view(n, k // 32, 32) * torch.exp2(e8.double() - 128).view(n, k // 32, 1)
+    w = w.view(n, k // 256, 256)
+    return torch.stack([w[:, b] @ q[i].double().view(-1, 256)[b] for i, b in enumerate(blocks)])
+
+
+def mx_upload(tq, c4, e8):
+    n, k = c4.shape
+    return tq.TqMatrixMx(n, k, torch.from_numpy(tq.tq_mx_pack_host(c4.to(torch.uint8).cpu().numpy())).cuda(), e8.to(torch.uint8))
+
+
+def mx_extreme(pattern, n, k, t, span):
+    """Codes, scales and activations of the largest magnitudes, scales over the whole span."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + t + span)
+    r = lambda lo, hi, sh: torch.randint(lo, hi, sh, device="cuda", generator=g)
+    e8 = 120 + span * r(0, 2, (n, k // 32))
+    q = (127 - r(0, 2, (t, k))) * torch.where(r(0, 2, (t, k)) == 0, -1, 1)
+    big = torch.where(r(0, 64, (n, k)) == 0, 1, 7)  # +-6, and a few of the smallest code
+    if pattern == "aligned":  # one sign throughout, the least scale in one chunk of eight
+        e8 = torch.where(torch.arange(k // 32, device="cuda") % 8 == torch.arange(n, device="cuda").view(n, 1) % 8, 120, 120 + span)
+        q = q.abs() * torch.where(torch.arange(t, device="cuda") % 2 == 0, 1, -1).view(t, 1)
+        return big, e8, q
+    if pattern == "cancelling":  # chunk pairs of the largest scale cancel to a few units of the least
+        e8 = 120 + span * torch.ones_like(e8)
+        e8[:, 2::4] = 120
+        big = big.view(n, k // 128, 4, 32)
+        big[:, :, 1] = big[:, :, 0] | 8
+        q = q.view(t, k // 128, 4, 32)
+        q[:, :, 1] = q[:, :, 0]
+        return big.reshape(n, k), e8, q.reshape(t, k)
+    return big | 8 * r(0, 2, (n, k)), e8, q
+
+
+@pytest.mark.parametrize("pattern", ["aligned", "cancelling", "mixed"])
+@pytest.mark.parametrize("tile", list(MX_TILES))
+def test_mx_block_sums_are_exact_over_the_span(tq, tile, pattern):
+    # the largest codes and activations, scales that span 2^8: a block's sum is exact and
+    # rounded to fp32 once (d = 1 for one block of each token, 0 for the others, so that y is
+    # that sum)
+    (n, t), k = MX_TILES[tile], 1280
+    announce(f"mx exact sums {tile} {pattern}")
+    c4, e8, q = mx_extreme(pattern, n, k, t, 8)
+    blocks = [(3 * i + 1) % 5 for i in range(t)]
+    d = torch.zeros((t, 5), device="cuda")
+    d[torch.arange(t), torch.tensor(blocks)] = 1.0
+    y = torch.full((t, n), float("nan"), device="cuda")
+    tq.tq_gemv_mx(mx_upload(tq, c4, e8), q.to(torch.int8), d, y)
+    assert torch.equal(y, mx_exact(c4, e8, q, blocks).float())
