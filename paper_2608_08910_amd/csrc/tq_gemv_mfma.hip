@@ -25,6 +25,8 @@
 // with 64 x 64 tiles, 16.3 with 64 rows x 32 tokens, VALU pass 142.6).
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 #include "tq_device.hpp"
 #include "tq_decode.hpp"
 #include "tq_internal.hpp"
@@ -72,11 +74,14 @@ __device__ __forceinline__ void wait_vmcnt() {
 // 256 x 8 x 12, in units of half the block's least scale; while the row block's scales span at
 // most 2^8, every partial sum is below 2^24 of these units, so both come out exact whatever the
 // unit's order, and their sum is rounded once. (One accumulator for both would keep that only to
-// a span of 2^5.) A row block of a wider span takes whole-number sums chunk by chunk, scaled one
-// by one: they need a decode of every code and a scaling of every 32-element sum (32768 x 4096,
-// 4 tokens: 20.4 us, 37.5 so, VALU pass 38.2; 2048 x 4096, 509 tokens: 25.8 us, 49 so, VALU pass
-// 151). Against 64 bits: 5.0e-8 to 5.7e-8 of the result's norm, 6.8e-8 to 7.4e-8 from whole-number
-// sums scaled chunk by chunk.
+// a span of 2^5.) A row block of a wider span, or of scales outside 2^+-63, goes in groups of
+// nine powers of two from its largest scale down, each exact and rounded once: the codes of the
+// other chunks as zeros, the scales relative to the group's. A wave that meets such a block goes
+// on from it in a second copy of the loop, so that the first keeps its registers (scales within
+// 2^8, random over 2^9 and over 2^20, VALU pass: 32768 x 4096, 4 tokens 19.4, 23.4, 26.1 and 35.4
+// us; 2048 x 4096, 509 tokens 22.9, 30.2, 35.3 and 150; whole-number sums scaled chunk by chunk,
+// in a pass of their own from the first block on, took 36.5 and 47.5). Against 64 bits: 5.0e-8 to
+// 5.7e-8 of the result's norm, 6.8e-8 to 7.4e-8 from whole-number sums scaled chunk by chunk.
 // ---------------------------------------------------------------------------------
 
 typedef int v8i __attribute__((ext_vector_type(8)));
@@ -143,7 +148,7 @@ __device__ __forceinline__ void dm_combine(const uint8_t* s_wave, int lnw, int64
 // scales. DBG: the instance that
 // stores the exact block sums (so that the others carry no store addresses).
 template <int FMT, int MTT, int RT, bool DBG>
-__global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(MTT == 1 && FMT != 2 && !DBG ? 4 : 2))) void k_gemv_mfma(
+__global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(MTT == 1 && (FMT != 2 || RT == 1) && !DBG ? 4 : 2))) void k_gemv_mfma(
     const uint8_t* __restrict__ codes, const void* __restrict__ scales, int n, int kb, int lnw,
     const int8_t* __restrict__ q, const float* __restrict__ d, int t, float* __restrict__ y,
     int32_t* __restrict__ isum_dbg) {
@@ -235,8 +240,10 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
 #pragma unroll
         for (int v = 0; v < 4; ++v) acc[mt][rt][v] = 0.0f;
 
-    bool exact = MX && DBG;  // MXFP4: the wave takes the exact pass below instead
-    for (int b = kg; b < kb && !exact; b += kDmWaves) {
+    // One block, whose loads are issued. FAR: MXFP4 rows of any scales; else false, with nothing
+    // taken, where a row's scales are too far apart or too large or small.
+    const auto block = [&](int b, auto far_tag) -> bool {
+      constexpr bool FAR = decltype(far_tag)::value;
       wait_vmcnt<kAfterX>();  // the block's activations are in LDS (its scales and codes may not be here yet)
       wave_lds_fence();
       v4i aop[MX ? 1 : MTT][2][2];
@@ -270,13 +277,13 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
       wave_lds_fence();
       __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));  // LDS reads done: the area may be refilled
       wave_lds_fence();
-      // MXFP4: the block's scales, and whether a row's span more than 2^8 (the unit's sums need
-      // not be exact then) or any is outside 2^+-63 (they could overflow, or lose bits that d
-      // brings back). Halves: E and 255 - E, maxima over the
+      // MXFP4: the block's scales, and (a bit per row tile) whether those of the lane's row span
+      // more than 2^8 (the unit's sums need not be exact then) or any is outside 2^+-63 (they
+      // could overflow, or lose bits that d brings back). Halves: E and 255 - E, maxima over the
       // row's eight chunks.
-      uint32_t es[MX ? RT : 1][2];
+      uint32_t es[MX ? RT : 1][2], far = 0;
+      uint32_t top[MX ? RT : 1], low[MX ? RT : 1];  // the row's largest and least
       if constexpr (MX) {
-        bool far = false;
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
           es[rt][0] = E[rt][0];
@@ -285,10 +292,11 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
           uint32_t m = max_u16x2(halves(es[rt][0]), halves(es[rt][1]));
           m = max_u16x2(m, (uint32_t)lane_xor_i<16>((int)m));
           m = max_u16x2(m, (uint32_t)lane_xor_i<32>((int)m));
-          const uint32_t hi = m & 0xFFFFu, lo = 255u - (m >> 16);
-          far |= (rt * 16 + li < nrows) & ((hi > 190u) | (lo < 64u) | (hi - lo > 8u));
+          top[rt] = m & 0xFFFFu;
+          low[rt] = 255u - (m >> 16);
+          far |= (uint32_t)((rt * 16 + li < nrows) & ((top[rt] > 190u) | (low[rt] < 64u) | (top[rt] - low[rt] > 8u))) << rt;
         }
-        exact = __any(far) != 0;
+        if (!FAR && __any(far)) return false;
       }
       fetch_x(b + kDmWaves);
       __builtin_amdgcn_sched_barrier(0);
@@ -309,42 +317,130 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
         fetch_w(b + kDmWaves, rt);
       };
       if constexpr (MX) {
-        if (exact) break;
-        {
-          v8i alo[MTT][2], ahi[MTT][2];
+        v8i alo[MTT][2], ahi[MTT][2];
 #pragma unroll
-          for (int mt = 0; mt < MTT; ++mt)
+        for (int mt = 0; mt < MTT; ++mt)
 #pragma unroll
-            for (int c = 0; c < 2; ++c)
+          for (int c = 0; c < 2; ++c) {
 #pragma unroll
-              for (int h = 0; h < 2; ++h) mx_acts(xa[mt][c][h], xb[mt][c][h], h, alo[mt][c], ahi[mt][c]);
+            for (int h = 0; h < 2; ++h) mx_acts(xa[mt][c][h], xb[mt][c][h], h, alo[mt][c], ahi[mt][c]);
+            // (one after the other: all at once they take more registers than this loop has)
+            if constexpr (FAR) asm volatile("" : "+v"(alo[mt][c]), "+v"(ahi[mt][c]));
+          }
+        // one row tile's products with the codes w and the scales s: each sum exact
+        const auto products = [&](const uint4 (&w)[2], const uint32_t (&s)[2], v4f (&C)[MTT]) {
+          v4f Ch[MTT];
+#pragma unroll
+          for (int mt = 0; mt < MTT; ++mt) C[mt] = Ch[mt] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            const v8i bw = {(int)w[c].x, (int)w[c].y, (int)w[c].z, (int)w[c].w, 0, 0, 0, 0};
+#pragma unroll
+            for (int mt = 0; mt < MTT; ++mt)
+              C[mt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(alo[mt][c], bw, C[mt], 0, 4, 0, kLoScale, 0, (int)s[c]);
+#pragma unroll
+            for (int mt = 0; mt < MTT; ++mt)
+              Ch[mt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ahi[mt][c], bw, Ch[mt], 0, 4, 0, kHiScale, 0, (int)s[c]);
+          }
+#pragma unroll
+          for (int mt = 0; mt < MTT; ++mt) C[mt] = C[mt] + Ch[mt];
+        };
+        if constexpr (!FAR) {
           stage_w(0);
 #pragma unroll
           for (int rt = 0; rt < RT; ++rt) {
             if (rt + 1 < RT) stage_w(rt + 1);
-            v4f Cl[MTT], Ch[MTT];  // each exact
-#pragma unroll
-            for (int mt = 0; mt < MTT; ++mt) Cl[mt] = Ch[mt] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-              const uint4 w = wt[rt & 1][c];
-              const v8i bw = {(int)w.x, (int)w.y, (int)w.z, (int)w.w, 0, 0, 0, 0};
-#pragma unroll
-              for (int mt = 0; mt < MTT; ++mt)
-                Cl[mt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(alo[mt][c], bw, Cl[mt], 0, 4, 0, kLoScale, 0, (int)es[rt][c]);
-#pragma unroll
-              for (int mt = 0; mt < MTT; ++mt)
-                Ch[mt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ahi[mt][c], bw, Ch[mt], 0, 4, 0, kHiScale, 0, (int)es[rt][c]);
-            }
+            v4f C[MTT];
+            products(wt[rt & 1], es[rt], C);
 #pragma unroll
             for (int mt = 0; mt < MTT; ++mt) {
               const float dv[4] = {d4[mt].x, d4[mt].y, d4[mt].z, d4[mt].w};
 #pragma unroll
-              for (int v = 0; v < 4; ++v) acc[mt][rt][v] = fmaf(dv[v], Cl[mt][v] + Ch[mt][v], acc[mt][rt][v]);
+              for (int v = 0; v < 4; ++v) acc[mt][rt][v] = fmaf(dv[v], C[mt][v], acc[mt][rt][v]);
             }
           }
+        } else {
+          // A far row takes its chunks in groups: scales 2^0 .. 2^-8 of its largest, 2^-9 .. 2^-17
+          // and so on, each group's sum exact and relative to the group. The other rows take all
+          // theirs in the first round, as above: a row's result is its own, whatever its
+          // neighbours' scales. (Two independent chains a round: two token tiles or two row tiles.)
+          constexpr int RP = RT < 2 || MTT > 1 ? 1 : 2;
+#pragma unroll
+          for (int r0 = 0; r0 < RT; r0 += RP) {
+            uint32_t grp[RP][2], last[RP];
+#pragma unroll
+            for (int r = 0; r < RP; ++r) {
+              const int rt = r0 + r;
+              stage_w(rt);
+              if constexpr (DBG) {
+            // the chunks' whole-number sums, two chunks (lanes g < 2, g >= 2) at a time, each with
+            // the other's codes as zeros: the activations stand in the order of the scaled operand
+            const uint8_t* const p = (rt % NB ? bt1 : bt0) + li * 128 + 8 * (g & 1);
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+              for (int h = 0; h < 2; ++h) {
+                const int j0 = 4 * c + 2 * h;
+                const uint2 x = *reinterpret_cast<const uint2*>(p + (((j0 + (g >> 1)) ^ ((li >> 1) & 7)) * 16));
+                const uint2 wl = {(uint32_t)mx_dec4(x.x & 0x07070707u, x.x << 4), (uint32_t)mx_dec4(x.y & 0x07070707u, x.y << 4)};
+                const uint2 wh = {(uint32_t)mx_dec4((x.x >> 4) & 0x07070707u, x.x), (uint32_t)mx_dec4((x.y >> 4) & 0x07070707u, x.y)};
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                  const bool own = (g >> 1) == j;
+                  const long bl = own ? __builtin_bit_cast(long, wl) : 0, bh = own ? __builtin_bit_cast(long, wh) : 0;
+#pragma unroll
+                  for (int mt = 0; mt < MTT; ++mt) {
+                    v4i C = {0, 0, 0, 0};
+                    C = __builtin_amdgcn_mfma_i32_16x16x32_i8(__builtin_bit_cast(long, xa[mt][c][h]), bl, C, 0, 0, 0);
+                    C = __builtin_amdgcn_mfma_i32_16x16x32_i8(__builtin_bit_cast(long, xb[mt][c][h]), bh, C, 0, 0, 0);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                      const int tok = mt * 16 + 4 * g + v, r = rt * 16 + li;
+                      if (tok < ntok && row0 + r < n)
+                        isum_dbg[((int64_t)(t0 + tok) * n + row0 + r) * (kb * 8) + b * 8 + j0 + j] = C[v];
+                    }
+                  }
+                }
+              }
+              }
+              const bool fr = (far >> rt) & 1u;
+              const auto group = [&](uint32_t e) { return (uint32_t)__mul24(fr ? top[rt] - e : 0u, 57) >> 9; };  // x / 9 of a byte x
+              grp[r][0] = group(es[rt][0]);
+              grp[r][1] = group(es[rt][1]);
+              last[r] = group(low[rt]);
+            }
+            uint32_t p = 0;
+            do {
+#pragma unroll
+              for (int r = 0; r < RP; ++r) {
+                const int rt = r0 + r;
+                const int sh = (far >> rt) & 1u ? (int)(top[rt] - 9 * p) - 128 : 0;
+                uint4 w[2];
+                uint32_t s[2];
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                  const bool take = grp[r][c] == p;
+                  const uint4 z = wt[rt & 1][c];
+                  w[c] = make_uint4(take ? z.x : 0u, take ? z.y : 0u, take ? z.z : 0u, take ? z.w : 0u);
+                  s[c] = take ? es[rt][c] - (uint32_t)sh : 127u;
+                }
+                v4f C[MTT];
+                products(w, s, C);
+#pragma unroll
+                for (int mt = 0; mt < MTT; ++mt) {
+                  const float dv[4] = {d4[mt].x, d4[mt].y, d4[mt].z, d4[mt].w};
+#pragma unroll
+                  for (int v = 0; v < 4; ++v) {
+                    const float a = fmaf(ldexpf(dv[v], sh), C[mt][v], acc[mt][rt][v]);
+                    acc[mt][rt][v] = p <= last[r] ? a : acc[mt][rt][v];  // (past its groups: also where d is infinite)
+                  }
+                }
+              }
+              ++p;
+            } while (__any(p <= (RP > 1 ? max(last[0], last[RP - 1]) : last[0])));
+          }
         }
-        continue;
+        return true;
       }
       stage_w(0);
 #pragma unroll
@@ -407,66 +503,15 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
             }
         }
       }
-    }
+      return true;
+    };
     if constexpr (MX) {
-      if (exact) {
-        // exact int8 sums per chunk, scaled one by one: lane (li, g) takes dword g of every
-        // 16 bytes (low nibbles: elements 4g .. 4g + 3, high nibbles: 16 + 4g ..)
-#pragma unroll
-        for (int mt = 0; mt < MTT; ++mt)
-#pragma unroll
-          for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[mt][rt][v] = 0.0f;
-        for (int b = kg; b < kb; b += kDmWaves) {
-          wait_vmcnt<0>();
-          wave_lds_fence();
-          fetch_x(b);
-          fetch_sd(b);
-#pragma unroll
-          for (int rt = 0; rt < RT; ++rt) fetch_w(b, rt);
-          wait_vmcnt<0>();
-          ssd[lane] = __float_as_uint(dd);
-          wave_lds_fence();
-          float4 d4[MTT];
-#pragma unroll
-          for (int mt = 0; mt < MTT; ++mt) d4[mt] = *reinterpret_cast<const float4*>(&ssd[mt * 16 + 4 * g]);
-#pragma unroll
-          for (int rt = 0; rt < RT; ++rt) {
-            const int wr = lane >> 3, rs = (li >> 1) & 7;
-            wave_lds_fence();
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-              *reinterpret_cast<uint4*>(bt0 + (8 * c + wr) * 128 + (((lane & 7) ^ (((8 * c + wr) >> 1) & 7)) * 16)) = W[rt][c];
-            wave_lds_fence();
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-#pragma unroll 1
-            for (int j = 4 * c; j < 4 * c + 4; ++j) {
-              const uint32_t x = *reinterpret_cast<const uint32_t*>(bt0 + li * 128 + ((j ^ rs) * 16) + 4 * g);
-              const int ex = __builtin_amdgcn_ds_bpermute((16 * (j & 3) + li) << 2, (int)E[rt][c]) - 128;
-              const uint32_t blo = (uint32_t)mx_dec4(x & 0x07070707u, x << 4), bhi = (uint32_t)mx_dec4((x >> 4) & 0x07070707u, x);
-#pragma unroll
-              for (int mt = 0; mt < MTT; ++mt) {
-                const uint8_t* const row = sa + (mt * 16 + li) * 256 + 4 * g;
-                const uint32_t a0 = *reinterpret_cast<const uint32_t*>(row + (((2 * j) ^ li) * 16));
-                const uint32_t a1 = *reinterpret_cast<const uint32_t*>(row + (((2 * j + 1) ^ li) * 16));
-                const v4i C = __builtin_amdgcn_mfma_i32_16x16x32_i8(
-                    (long)(a0 | ((uint64_t)a1 << 32)), (long)(blo | ((uint64_t)bhi << 32)), v4i{0, 0, 0, 0}, 0, 0, 0);
-                const float dv[4] = {d4[mt].x, d4[mt].y, d4[mt].z, d4[mt].w};
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                  acc[mt][rt][v] = fmaf(ldexpf(dv[v], ex), (float)C[v], acc[mt][rt][v]);
-                  const int tok = mt * 16 + 4 * g + v, r = rt * 16 + li;
-                  if (DBG && tok < ntok && row0 + r < n)
-                    isum_dbg[((int64_t)(t0 + tok) * n + row0 + r) * (kb * 8) + b * 8 + j] = C[v];
-                }
-              }
-            }
-          }
-          wave_lds_fence();
-        }
-      }
+      int b = kg;
+      if constexpr (!DBG)
+        while (b < kb && block(b, std::false_type{})) b += kDmWaves;
+      for (; b < kb; b += kDmWaves) block(b, std::true_type{});  // (on from the first such block)
+    } else {
+      for (int b = kg; b < kb; b += kDmWaves) block(b, std::false_type{});
     }
     // (the last, empty refills of the activations have landed before the area is reused)
     wait_vmcnt<0>();

@@ -3,8 +3,8 @@ than one token) against the single-token kernels on the same quantized activatio
 
 Bar: exact block sums equal and y bitwise equal, token by token: both take each row's fp32
 block terms in the same order (the single-token kernels' own parity with the oracle is
-asserted in their tests). MXFP4 takes its block sums on the scaled fp8 x fp4 unit (with the
-block-sum output, or scales of a wide span, as exact whole numbers scaled one by one): y against the oracle, within 1e-6 of the absolute terms (a term's
+asserted in their tests). MXFP4 takes its block sums on the scaled fp8 x fp4 unit (scales
+of a wide span in groups): y against the oracle, within 1e-6 of the absolute terms (a term's
 fp32 roundings of 2^-24 on its way into the sum: at most 8 per block over a wave's 8 blocks at
 k = 16384, where they average out, and 4 + 5 + 3 at k = 1280 x 4; 16 of them are 1e-6)."""
 import numpy as np
@@ -90,8 +90,8 @@ def check_mx_tokens(tq, oracle, m, q, d, y):
     assert_close(y[i].cpu().numpy(), yr, ar, rtol=1e-6, what="y")
 
 
-# scales of a span up to 2^8 (the scaled unit), wider or beyond 2^+-63 (the whole-number pass),
-# and both within a matrix; a ragged last row tile must not read as far scales
+# scales of a span up to 2^8 (all at once), wider or beyond 2^+-63 (in groups), and both within
+# a matrix; a ragged last row tile must not read as far scales
 @pytest.mark.parametrize("e_lo,e_hi", [(116, 125), (116, 126), (64, 191), (20, 236), (62, 67), (188, 193)])
 @pytest.mark.parametrize("n,k,t", [(70, 1280, 5), (8205, 256, 9), (4107, 2304, 17), (300, 768, 40)])
 def test_mx_scale_range(tq, oracle, n, k, t, e_lo, e_hi):
@@ -161,3 +161,71 @@ def test_mx_block_sums_are_exact_over_the_span(tq, tile, pattern):
     y = torch.full((t, n), float("nan"), device="cuda")
     tq.tq_gemv_mx(mx_upload(tq, c4, e8), q.to(torch.int8), d, y)
     assert torch.equal(y, mx_exact(c4, e8, q, blocks).float())
+
+
+def mx_groups(e8, k):
+    """Group of each chunk's scale ([n][k/32]) by the rule of tq.h: all 0 in a block whose scales span at most
+    2^8 within 2^+-63, else by distance from the block's largest, nine powers of two a group."""
+    e = e8.view(e8.shape[0], k // 256, 8).int()
+    hi, lo = e.amax(2, keepdim=True), e.amin(2, keepdim=True)
+    far = (hi > 190) | (lo < 64) | (hi - lo > 8)
+    return torch.where(far, (hi - e) // 9, 0).view(e8.shape)
+
+
+@pytest.mark.parametrize("e_lo,e_hi", [(100, 110), (100, 126), (40, 64), (185, 205)])
+@pytest.mark.parametrize("tile", list(MX_TILES))
+def test_mx_far_scales_add_group_by_group(tq, tile, e_lo, e_hi):
+    # scales too far apart or too large or small: each group's sum exact and rounded once, added
+    # from the largest scales down (d = 1 for one block of each token, 0 for the others; the fp64
+    # sums here are exact: below 2^(19 + 26) units)
+    (n, t), k = MX_TILES[tile], 1280
+    announce(f"mx far scales {tile} {e_lo}..{e_hi}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + t + e_lo)
+    c4 = torch.randint(0, 16, (n, k), device="cuda", generator=g)
+    e8 = torch.randint(e_lo, e_hi, (n, k // 32), device="cuda", generator=g)
+    q = torch.randint(-127, 128, (t, k), device="cuda", generator=g)
+    blocks = [(3 * i + 1) % 5 for i in range(t)]
+    d = torch.zeros((t, 5), device="cuda")
+    d[torch.arange(t), torch.tensor(blocks)] = 1.0
+    y = torch.full((t, n), float("nan"), device="cuda")
+    tq.tq_gemv_mx(mx_upload(tq, c4, e8), q.to(torch.int8), d, y)
+    grp = mx_groups(e8, k).repeat_interleave(32, 1)
+    want = torch.zeros((t, n), device="cuda")
+    for p in range(int(grp.max()) + 1):
+        want = (want.double() + mx_exact(torch.where(grp == p, c4, 0), e8, q, blocks).float().double()).float()
+    assert torch.equal(y, want)
+
+
+@pytest.mark.parametrize("k", [256, 1024, 2304, 5120])
+@pytest.mark.parametrize("tile", list(MX_TILES))
+def test_mx_rows_are_their_own(tq, tile, k):
+    # a row's bits depend neither on its neighbours' scales (near ones among far ones and the
+    # other way round, far in some of their blocks) nor on the block-sum output
+    n, t = MX_TILES[tile]
+    announce(f"mx rows {tile} k={k}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + t + k)
+    c4 = torch.randint(0, 16, (n, k), device="cuda", generator=g)
+    near = torch.randint(116, 125, (n, k // 32), device="cuda", generator=g)
+    far = torch.where(torch.rand((n, k // 256, 1), device="cuda", generator=g).repeat(1, 1, 8).view(n, -1) < 0.5,
+                      torch.randint(104, 132, (n, k // 32), device="cuda", generator=g), near)
+    q = torch.randint(-127, 128, (t, k), device="cuda", generator=g).to(torch.int8)
+    d = torch.rand((t, k // 256), device="cuda", generator=g)
+
+    def run(e8, s=None):
+        y = torch.full((t, n), float("nan"), device="cuda")
+        tq.tq_gemv_mx(mx_upload(tq, c4, e8), q, d, y, s)
+        return y
+
+    sums = lambda: torch.full((t, n, k // 32), -1, dtype=torch.int32, device="cuda")
+    y_near, y_far = run(near), run(far)
+    for share in (1 / 16, 1 / 2, 15 / 16):
+        pick = torch.rand(n, device="cuda", generator=g) < share
+        e8, s = torch.where(pick.view(n, 1), far, near), sums()
+        y = run(e8)
+        assert torch.equal(y, torch.where(pick, y_far, y_near))
+        assert torch.equal(y, run(e8, s)), "debug output changes y"
+        w = DOUBLED.cuda()[c4].view(n, k // 32, 32).float()  # exact in fp32 (below 2^16)
+        i = t // 2
+        assert torch.equal(s[i], (w * q[i].float().view(k // 32, 32)).sum(2).int()), "block sums"
