@@ -291,9 +291,9 @@ tq_status tq_mx_unpack_host(const uint8_t* codes, int32_t n, int32_t k, uint8_t*
 
 /* The MXFP4 arm's pass for one matrix and t tokens (formula above). Several tokens take a
  * 256-column block's sum (on the scaled fp8 x fp4 matrix unit), exact and rounded to fp32 once,
- * times d, where the row's scales in it span at most 2^8 within 2^+-63; else in groups of scales
- * (the largest down to 2^-8 of it, then 2^-9 .. 2^-17 of it, ...), each such a sum. One token,
- * and few on a small matrix, take 32-element sums one by one, so the fp32 result may differ
+ * times d, where the row's scales in it span at most 2^8 within 2^+-63; else the fp32 sum of such
+ * sums over groups of scales (the largest down to 2^-8 of it, then 2^-9 .. 2^-17 of it, ...). One
+ * token, and few on a small matrix, take 32-element sums one by one, so the fp32 result may differ
  * between the two in its last bits. A row's result depends on its own scales alone. q, d as from
  * tq_quantize_act (q 16-byte aligned). isum_dbg: NULL, or a [t][n][k/32] int32 buffer
  * that receives the exact 32-element block sums. n >= 1, 256 <= k <= 16384, t >= 0. */

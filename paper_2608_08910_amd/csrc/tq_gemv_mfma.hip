@@ -78,10 +78,12 @@ __device__ __forceinline__ void wait_vmcnt() {
 // nine powers of two from its largest scale down, each exact and rounded once: the codes of the
 // other chunks as zeros, the scales relative to the group's. A wave that meets such a block goes
 // on from it in a second copy of the loop, so that the first keeps its registers (scales within
-// 2^8, random over 2^9 and over 2^20, VALU pass: 32768 x 4096, 4 tokens 19.4, 23.4, 26.1 and 35.4
-// us; 2048 x 4096, 509 tokens 22.9, 30.2, 35.3 and 150; whole-number sums scaled chunk by chunk,
-// in a pass of their own from the first block on, took 36.5 and 47.5). Against 64 bits: 5.0e-8 to
-// 5.7e-8 of the result's norm, 6.8e-8 to 7.4e-8 from whole-number sums scaled chunk by chunk.
+// 2^8, random over 2^9 and over 2^20, VALU pass: 32768 x 4096, 4 tokens 19.4, 23.1, 25.6 and 35.4
+// us; 2048 x 4096, 509 tokens 23.1, 30.8, 35.6 and 150; whole-number sums scaled chunk by chunk,
+// in a pass of their own from the first block on, took 36.5 and 47.5). Against 64 bits, in parts
+// of the result's norm, 512 x 16384 and 2048 x 4096: 7.2e-8 and 5.6e-8 for scales within 2^8, 7.9e-8
+// and 6.4e-8 over 2^20; VALU pass 8.5e-8 and 7.3e-8 (chunk by chunk into one sum, over 2^20: 15e-8
+// and 8.7e-8).
 // ---------------------------------------------------------------------------------
 
 typedef int v8i __attribute__((ext_vector_type(8)));
@@ -282,7 +284,7 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
       // could overflow, or lose bits that d brings back). Halves: E and 255 - E, maxima over the
       // row's eight chunks.
       uint32_t es[MX ? RT : 1][2], far = 0;
-      uint32_t top[MX ? RT : 1], low[MX ? RT : 1];  // the row's largest and least
+      uint32_t top[MX ? RT : 1];  // the row's largest
       if constexpr (MX) {
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
@@ -293,8 +295,8 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
           m = max_u16x2(m, (uint32_t)lane_xor_i<16>((int)m));
           m = max_u16x2(m, (uint32_t)lane_xor_i<32>((int)m));
           top[rt] = m & 0xFFFFu;
-          low[rt] = 255u - (m >> 16);
-          far |= (uint32_t)((rt * 16 + li < nrows) & ((top[rt] > 190u) | (low[rt] < 64u) | (top[rt] - low[rt] > 8u))) << rt;
+          const uint32_t low = 255u - (m >> 16);
+          far |= (uint32_t)((rt * 16 + li < nrows) & ((top[rt] > 190u) | (low < 64u) | (top[rt] - low > 8u))) << rt;
         }
         if (!FAR && __any(far)) return false;
       }
@@ -361,60 +363,64 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
           }
         } else {
           // A far row takes its chunks in groups: scales 2^0 .. 2^-8 of its largest, 2^-9 .. 2^-17
-          // and so on, each group's sum exact and relative to the group. The other rows take all
-          // theirs in the first round, as above: a row's result is its own, whatever its
-          // neighbours' scales. (Two independent chains a round: two token tiles or two row tiles.)
+          // and so on, each group's sum exact and relative to the group; added up, largest first,
+          // they meet d once, as a near row's. The other rows take all theirs in the first round,
+          // as above: a row's result is its own, whatever its neighbours' scales. (Two independent
+          // chains a round: two token tiles or two row tiles.)
           constexpr int RP = RT < 2 || MTT > 1 ? 1 : 2;
 #pragma unroll
           for (int r0 = 0; r0 < RT; r0 += RP) {
-            uint32_t grp[RP][2], last[RP];
+            uint32_t grp[RP][2];
+            v4f sum[RP][MTT];
 #pragma unroll
             for (int r = 0; r < RP; ++r) {
               const int rt = r0 + r;
               stage_w(rt);
               if constexpr (DBG) {
-            // the chunks' whole-number sums, two chunks (lanes g < 2, g >= 2) at a time, each with
-            // the other's codes as zeros: the activations stand in the order of the scaled operand
-            const uint8_t* const p = (rt % NB ? bt1 : bt0) + li * 128 + 8 * (g & 1);
+                // the chunks' whole-number sums, two chunks (lanes g < 2, g >= 2) at a time, each with
+                // the other's codes as zeros: the activations stand in the order of the scaled operand
+                const uint8_t* const p = (rt % NB ? bt1 : bt0) + li * 128 + 8 * (g & 1);
 #pragma unroll
-            for (int c = 0; c < 2; ++c)
+                for (int c = 0; c < 2; ++c)
 #pragma unroll
-              for (int h = 0; h < 2; ++h) {
-                const int j0 = 4 * c + 2 * h;
-                const uint2 x = *reinterpret_cast<const uint2*>(p + (((j0 + (g >> 1)) ^ ((li >> 1) & 7)) * 16));
-                const uint2 wl = {(uint32_t)mx_dec4(x.x & 0x07070707u, x.x << 4), (uint32_t)mx_dec4(x.y & 0x07070707u, x.y << 4)};
-                const uint2 wh = {(uint32_t)mx_dec4((x.x >> 4) & 0x07070707u, x.x), (uint32_t)mx_dec4((x.y >> 4) & 0x07070707u, x.y)};
+                  for (int h = 0; h < 2; ++h) {
+                    const int j0 = 4 * c + 2 * h;
+                    const uint2 x = *reinterpret_cast<const uint2*>(p + (((j0 + (g >> 1)) ^ ((li >> 1) & 7)) * 16));
+                    const uint2 wl = {(uint32_t)mx_dec4(x.x & 0x07070707u, x.x << 4), (uint32_t)mx_dec4(x.y & 0x07070707u, x.y << 4)};
+                    const uint2 wh = {(uint32_t)mx_dec4((x.x >> 4) & 0x07070707u, x.x), (uint32_t)mx_dec4((x.y >> 4) & 0x07070707u, x.y)};
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                  const bool own = (g >> 1) == j;
-                  const long bl = own ? __builtin_bit_cast(long, wl) : 0, bh = own ? __builtin_bit_cast(long, wh) : 0;
+                    for (int j = 0; j < 2; ++j) {
+                      const bool own = (g >> 1) == j;
+                      const long bl = own ? __builtin_bit_cast(long, wl) : 0, bh = own ? __builtin_bit_cast(long, wh) : 0;
 #pragma unroll
-                  for (int mt = 0; mt < MTT; ++mt) {
-                    v4i C = {0, 0, 0, 0};
-                    C = __builtin_amdgcn_mfma_i32_16x16x32_i8(__builtin_bit_cast(long, xa[mt][c][h]), bl, C, 0, 0, 0);
-                    C = __builtin_amdgcn_mfma_i32_16x16x32_i8(__builtin_bit_cast(long, xb[mt][c][h]), bh, C, 0, 0, 0);
+                      for (int mt = 0; mt < MTT; ++mt) {
+                        v4i C = {0, 0, 0, 0};
+                        C = __builtin_amdgcn_mfma_i32_16x16x32_i8(__builtin_bit_cast(long, xa[mt][c][h]), bl, C, 0, 0, 0);
+                        C = __builtin_amdgcn_mfma_i32_16x16x32_i8(__builtin_bit_cast(long, xb[mt][c][h]), bh, C, 0, 0, 0);
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                      const int tok = mt * 16 + 4 * g + v, r = rt * 16 + li;
-                      if (tok < ntok && row0 + r < n)
-                        isum_dbg[((int64_t)(t0 + tok) * n + row0 + r) * (kb * 8) + b * 8 + j0 + j] = C[v];
+                        for (int v = 0; v < 4; ++v) {
+                          const int tok = mt * 16 + 4 * g + v, r = rt * 16 + li;
+                          if (tok < ntok && row0 + r < n)
+                            isum_dbg[((int64_t)(t0 + tok) * n + row0 + r) * (kb * 8) + b * 8 + j0 + j] = C[v];
+                        }
+                      }
                     }
                   }
-                }
-              }
               }
               const bool fr = (far >> rt) & 1u;
-              const auto group = [&](uint32_t e) { return (uint32_t)__mul24(fr ? top[rt] - e : 0u, 57) >> 9; };  // x / 9 of a byte x
+              // (x * 57 >> 9 is x / 9 for a byte x)
+              const auto group = [&](uint32_t e) { return (uint32_t)__mul24(fr ? top[rt] - e : 0u, 57) >> 9; };
               grp[r][0] = group(es[rt][0]);
               grp[r][1] = group(es[rt][1]);
-              last[r] = group(low[rt]);
+#pragma unroll
+              for (int mt = 0; mt < MTT; ++mt) sum[r][mt] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
             }
             uint32_t p = 0;
             do {
 #pragma unroll
               for (int r = 0; r < RP; ++r) {
                 const int rt = r0 + r;
-                const int sh = (far >> rt) & 1u ? (int)(top[rt] - 9 * p) - 128 : 0;
+                const uint32_t unit = (far >> rt) & 1u ? top[rt] - 9 * p - 128 : 0u;
                 uint4 w[2];
                 uint32_t s[2];
 #pragma unroll
@@ -422,22 +428,28 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
                   const bool take = grp[r][c] == p;
                   const uint4 z = wt[rt & 1][c];
                   w[c] = make_uint4(take ? z.x : 0u, take ? z.y : 0u, take ? z.z : 0u, take ? z.w : 0u);
-                  s[c] = take ? es[rt][c] - (uint32_t)sh : 127u;
+                  s[c] = take ? es[rt][c] - unit : 127u;
                 }
                 v4f C[MTT];
                 products(w, s, C);
 #pragma unroll
-                for (int mt = 0; mt < MTT; ++mt) {
-                  const float dv[4] = {d4[mt].x, d4[mt].y, d4[mt].z, d4[mt].w};
+                for (int mt = 0; mt < MTT; ++mt)
 #pragma unroll
-                  for (int v = 0; v < 4; ++v) {
-                    const float a = fmaf(ldexpf(dv[v], sh), C[mt][v], acc[mt][rt][v]);
-                    acc[mt][rt][v] = p <= last[r] ? a : acc[mt][rt][v];  // (past its groups: also where d is infinite)
-                  }
-                }
+                  for (int v = 0; v < 4; ++v) sum[r][mt][v] += ldexpf(C[mt][v], -9 * (int)p);
               }
               ++p;
-            } while (__any(p <= (RP > 1 ? max(last[0], last[RP - 1]) : last[0])));
+            } while (__any(p <= (RP > 1 ? max(max(grp[0][0], grp[0][1]), max(grp[RP - 1][0], grp[RP - 1][1]))
+                                        : max(grp[0][0], grp[0][1]))));
+#pragma unroll
+            for (int r = 0; r < RP; ++r) {
+              const int rt = r0 + r, sh = (far >> rt) & 1u ? (int)top[rt] - 128 : 0;
+#pragma unroll
+              for (int mt = 0; mt < MTT; ++mt) {
+                const float dv[4] = {d4[mt].x, d4[mt].y, d4[mt].z, d4[mt].w};
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[mt][rt][v] = fmaf(ldexpf(dv[v], sh), sum[r][mt][v], acc[mt][rt][v]);
+              }
+            }
           }
         }
         return true;

@@ -176,7 +176,7 @@ def mx_groups(e8, k):
 @pytest.mark.parametrize("tile", list(MX_TILES))
 def test_mx_far_scales_add_group_by_group(tq, tile, e_lo, e_hi):
     # scales too far apart or too large or small: each group's sum exact and rounded once, added
-    # from the largest scales down (d = 1 for one block of each token, 0 for the others; the fp64
+    # up from the largest scales down, before d (d = 1 for one block of each token, 0 for the others; the fp64
     # sums here are exact: below 2^(19 + 26) units)
     (n, t), k = MX_TILES[tile], 1280
     announce(f"mx far scales {tile} {e_lo}..{e_hi}")
@@ -229,3 +229,24 @@ def test_mx_rows_are_their_own(tq, tile, k):
         w = DOUBLED.cuda()[c4].view(n, k // 32, 32).float()  # exact in fp32 (below 2^16)
         i = t // 2
         assert torch.equal(s[i], (w * q[i].float().view(k // 32, 32)).sum(2).int()), "block sums"
+
+
+@pytest.mark.parametrize("e_lo,e_hi", [(116, 125), (110, 131), (20, 60)])
+@pytest.mark.parametrize("n,k,t", [(512, 16384, 40), (2048, 4096, 17)])
+def test_mx_loses_no_precision(tq, n, k, t, e_lo, e_hi):
+    # error against fp64 no larger than that of the single-token pass on the same data
+    announce(f"mx precision n={n} k={k} t={t} {e_lo}..{e_hi}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    c4 = torch.randint(0, 16, (n, k), device="cuda", generator=g)
+    e8 = torch.randint(e_lo, e_hi, (n, k // 32), device="cuda", generator=g)
+    q = torch.randint(-127, 128, (t, k), device="cuda", generator=g).to(torch.int8)
+    d = torch.rand((t, k // 256), device="cuda", generator=g)
+    m = mx_upload(tq, c4, e8)
+    y, y1 = torch.empty((t, n), device="cuda"), torch.empty((t, n), device="cuda")
+    tq.tq_gemv_mx(m, q, d, y)
+    for i in range(t):
+        tq.tq_gemv_mx(m, q[i:i + 1], d[i:i + 1], y1[i:i + 1])
+    w = DOUBLED.cuda()[c4].view(n, k // 32, 32) * torch.exp2(e8.double() - 128).view(n, k // 32, 1)
+    r = (q.double().view(t, k // 256, 256) * d.double().view(t, -1, 1)).view(t, k) @ w.view(n, k).t()
+    assert float((y - r).norm()) <= float((y1 - r).norm())
