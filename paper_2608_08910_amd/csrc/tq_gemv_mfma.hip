@@ -25,6 +25,7 @@
 // with 64 x 64 tiles, 16.3 with 64 rows x 32 tokens, VALU pass 142.6).
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "tq_device.hpp"
@@ -557,16 +558,25 @@ void launch_gemv_mfma(int fmt, const uint8_t* codes, const void* scales, int n, 
   // workgroups), 5.6 at 2 x 1 (256), 6.2 at 2 x 2 (128), 8.3 at 2 x 4; 8192 x 4096, 128
   // tokens: 37.6 at 1 x 1, 18.3 at 2 x 4, 15.2 at 4 x 4). A larger tile reads fewer bytes per
   // output; one of more 16-token tiles than t fills computes padding. (Two planes: 4 x 4
-  // does not fit the registers. MXFP4: the activations' split into fp8 pairs costs as much as four row tiles' MFMAs, so 1 x 4 beats 1 x 2 at 16
-  // tokens and fewer: 21 against 24 us at 32768 x 4096, 4 tokens.)
+  // does not fit the registers.)
   struct Tile { int mtt, rt; };
   static constexpr Tile kTiles[] = {{4, 4}, {2, 4}, {2, 2}, {2, 1}, {1, 2}, {1, 1}};
-  static constexpr Tile kTilesMx[] = {{2, 4}, {2, 2}, {2, 1}, {1, 4}, {1, 2}, {1, 1}};
+  static constexpr Tile kTilesMx[] = {{2, 4}, {2, 2}, {2, 1}, {1, 4}, {1, 2}, {1, 1}};  // (the last three up to 16 tokens)
   const Tile* tiles = fmt == 2 ? kTilesMx : (fmt == 0 ? kTiles : kTiles + 1);
   const auto wgs = [&](int rt) { return ((((int64_t)n + 16 * rt - 1) / (16 * rt)) + (1 << (3 - lnw)) - 1) >> (3 - lnw); };
   const auto ttiles = [&](int mtt) { return ((int64_t)t + 16 * mtt - 1) / (16 * mtt); };
   while ((tiles->mtt > 1 && t <= 8 * tiles->mtt) || (tiles->mtt * tiles->rt > 1 && wgs(tiles->rt) * ttiles(tiles->mtt) < 256))
     ++tiles;
+  // MXFP4 at 16 tokens and fewer: the activations' split into fp8 pairs costs about as much as four
+  // row tiles' MFMAs, so a compute unit's share counts, workgroups by the cost of one (1 x 1 5,
+  // 1 x 2 10, 1 x 4 17): with 4 tokens 1 x 4 takes 19.5 us at 32768 x 4096 (1 x 2 22.0, 1 x 1 23.3)
+  // and 9.8 at 16384 x 4096 (11.1, 12.2), 1 x 2 6.4 at 8192 x 4096 (1 x 4 9.8), and where a few
+  // workgroups would begin another round 1 x 1: 8205 x 4096 8.8 (1 x 2 10.0, 1 x 4 9.7, VALU chunks
+  // with their own tile for it 8.5), 16610 x 1024 7.1 (8.0, 6.7, 7.2), 33000 x 1024 9.8 (11.2, 12.0, 11.3).
+  if (fmt == 2 && t <= 16) {
+    const auto cost = [&](int rt) { return (wgs(rt) + 255) / 256 * (rt == 4 ? 17 : 5 * rt); };
+    tiles = kTilesMx + (cost(4) <= std::min(cost(2), cost(1)) ? 3 : (cost(2) <= cost(1) ? 4 : 5));
+  }
   const int mtt = tiles->mtt, rt = tiles->rt;
   const int64_t ntt = ttiles(mtt);
   // several token tiles: a multiple of 8 row tiles, so that a row tile's workgroups share an XCD
