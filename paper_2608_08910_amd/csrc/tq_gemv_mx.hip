@@ -32,7 +32,8 @@ __device__ __forceinline__ int mx_dot32(const uint4 w, const int (&a)[8]) {
   return acc;
 }
 
-// One chunk of at most NT tokens (blockIdx.y: which; more tokens: tq_gemv_mfma.hip).
+// One chunk of at most NT tokens (blockIdx.y: which) of at most 16, with 32-bit offsets into q and d
+// (more tokens: tq_gemv_mfma.hip).
 template <int NL, int NT, int RPW>
 __global__ __launch_bounds__(256) void k_gemv_mx(const uint8_t* __restrict__ codes, const uint8_t* __restrict__ scales,
                                                  int n, int kb, const int8_t* __restrict__ q,
@@ -46,13 +47,7 @@ __global__ __launch_bounds__(256) void k_gemv_mx(const uint8_t* __restrict__ cod
   const int g = lane >> 3, cp = lane & 7;
   const int row0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * RPW;
   if (row0 >= n) return;
-  const int64_t k = (int64_t)kb * 256;
-  const int64_t c0 = (int64_t)blockIdx.y * NT;
-  q += c0 * k;
-  d += c0 * kb;
-  y += c0 * n;
-  if (isum_dbg != nullptr) isum_dbg += c0 * n * (kb * 8);
-  t -= (int)c0;
+  const int t0 = blockIdx.y * NT;
 
   // The activations and block scales, requested before the weights (a compute unit returns
   // loads in issue order).
@@ -62,8 +57,8 @@ __global__ __launch_bounds__(256) void k_gemv_mx(const uint8_t* __restrict__ cod
   for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
-      const int64_t tc = min(tt, t - 1);
-      const int4* p = reinterpret_cast<const int4*>(q + tc * k + min(8 * i + g, kb - 1) * 256 + cp * 32);
+      const int tc = min(t0 + tt, t - 1);
+      const int4* p = reinterpret_cast<const int4*>(q + (tc * kb + min(8 * i + g, kb - 1)) * 256 + cp * 32);
       const int4 lo = p[0], hi = p[1];
       qa[tt][i][0] = lo.x; qa[tt][i][1] = lo.y; qa[tt][i][2] = lo.z; qa[tt][i][3] = lo.w;
       qa[tt][i][4] = hi.x; qa[tt][i][5] = hi.y; qa[tt][i][6] = hi.z; qa[tt][i][7] = hi.w;
@@ -102,10 +97,10 @@ __global__ __launch_bounds__(256) void k_gemv_mx(const uint8_t* __restrict__ cod
 #pragma unroll
       for (int tt = 0; tt < NT; ++tt) {
         const int is = mx_dot32(w[r][i], qa[tt][i]);  // the block's exact sum
-        const float dv = (tt < t && b < kb) ? dt[tt][i] : 0.0f;
+        const float dv = (t0 + tt < t && b < kb) ? dt[tt][i] : 0.0f;
         acc[r * NT + tt] = fmaf(ldexpf(dv, ex[r][i] - 128), (float)is, acc[r * NT + tt]);
         if (isum_dbg != nullptr) {
-          const int tok = tt, row = row0 + r;
+          const int tok = t0 + tt, row = row0 + r;
           if (tok < t && row < n && b < kb) isum_dbg[((int64_t)tok * n + row) * (kb * 8) + b * 8 + cp] = is;
         }
       }
@@ -126,7 +121,7 @@ __global__ __launch_bounds__(256) void k_gemv_mx(const uint8_t* __restrict__ cod
   }
   RR::block_totals(kept);
   if (RR::writer(lane)) {
-    const int it = RR::item(lane), tok = it % NT, row = row0 + it / NT;
+    const int it = RR::item(lane), tok = t0 + it % NT, row = row0 + it / NT;
     if (tok < t && row < n) y[(int64_t)tok * n + row] = kept[0];
   }
 }
