@@ -577,32 +577,44 @@ void launch_gemv_mfma(int fmt, const uint8_t* codes, const void* scales, int n, 
     const auto cost = [&](int rt) { return (wgs(rt) + 255) / 256 * (rt == 4 ? 17 : 5 * rt); };
     tiles = kTilesMx + (cost(4) <= std::min(cost(2), cost(1)) ? 3 : (cost(2) <= cost(1) ? 4 : 5));
   }
-  const int mtt = tiles->mtt, rt = tiles->rt;
+  // The block sums' addresses take registers of their own: their instances go up to the tiles
+  // that hold them without spilling (4 x 4 would spill 315).
+  const int mtt = isum_dbg ? std::min(tiles->mtt, fmt == 2 ? 1 : 2) : tiles->mtt;
+  const int rt = isum_dbg ? std::min(tiles->rt, 2) : tiles->rt;
   const int64_t ntt = ttiles(mtt);
   // several token tiles: a multiple of 8 row tiles, so that a row tile's workgroups share an XCD
   const int64_t gx = ntt > 1 ? (wgs(rt) + 7) / 8 * 8 : wgs(rt);
   const dim3 grid((unsigned)gx, (unsigned)(ntt < 16384 ? ntt : 16384));
-#define TQ_DM(F, M, R)                                                                                                  \
-  dm_launch(isum_dbg ? k_gemv_mfma<F, M, R, true> : k_gemv_mfma<F, M, R, false>, grid, st, events, codes, scales, n, kb, \
-            lnw, q, d, t, y, isum_dbg)
-  switch (fmt * 100 + mtt * 10 + rt) {
-    case 11: TQ_DM(0, 1, 1); break;
-    case 12: TQ_DM(0, 1, 2); break;
-    case 21: TQ_DM(0, 2, 1); break;
-    case 22: TQ_DM(0, 2, 2); break;
-    case 24: TQ_DM(0, 2, 4); break;
-    case 44: TQ_DM(0, 4, 4); break;
-    case 111: TQ_DM(1, 1, 1); break;
-    case 112: TQ_DM(1, 1, 2); break;
-    case 121: TQ_DM(1, 2, 1); break;
-    case 122: TQ_DM(1, 2, 2); break;
-    case 124: TQ_DM(1, 2, 4); break;
-    case 211: TQ_DM(2, 1, 1); break;
-    case 212: TQ_DM(2, 1, 2); break;
-    case 214: TQ_DM(2, 1, 4); break;
-    case 221: TQ_DM(2, 2, 1); break;
-    case 222: TQ_DM(2, 2, 2); break;
-    default: TQ_DM(2, 2, 4); break;
+#define TQ_DM(F, M, R, D) \
+  dm_launch(k_gemv_mfma<F, M, R, D>, grid, st, events, codes, scales, n, kb, lnw, q, d, t, y, isum_dbg)
+  switch ((isum_dbg ? 1000 : 0) + fmt * 100 + mtt * 10 + rt) {
+    case 11: TQ_DM(0, 1, 1, false); break;
+    case 12: TQ_DM(0, 1, 2, false); break;
+    case 21: TQ_DM(0, 2, 1, false); break;
+    case 22: TQ_DM(0, 2, 2, false); break;
+    case 24: TQ_DM(0, 2, 4, false); break;
+    case 44: TQ_DM(0, 4, 4, false); break;
+    case 111: TQ_DM(1, 1, 1, false); break;
+    case 112: TQ_DM(1, 1, 2, false); break;
+    case 121: TQ_DM(1, 2, 1, false); break;
+    case 122: TQ_DM(1, 2, 2, false); break;
+    case 124: TQ_DM(1, 2, 4, false); break;
+    case 211: TQ_DM(2, 1, 1, false); break;
+    case 212: TQ_DM(2, 1, 2, false); break;
+    case 214: TQ_DM(2, 1, 4, false); break;
+    case 221: TQ_DM(2, 2, 1, false); break;
+    case 222: TQ_DM(2, 2, 2, false); break;
+    case 224: TQ_DM(2, 2, 4, false); break;
+    case 1011: TQ_DM(0, 1, 1, true); break;
+    case 1012: TQ_DM(0, 1, 2, true); break;
+    case 1021: TQ_DM(0, 2, 1, true); break;
+    case 1022: TQ_DM(0, 2, 2, true); break;
+    case 1111: TQ_DM(1, 1, 1, true); break;
+    case 1112: TQ_DM(1, 1, 2, true); break;
+    case 1121: TQ_DM(1, 2, 1, true); break;
+    case 1122: TQ_DM(1, 2, 2, true); break;
+    case 1211: TQ_DM(2, 1, 1, true); break;
+    default: TQ_DM(2, 1, 2, true); break;
   }
 #undef TQ_DM
 }
