@@ -243,50 +243,53 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
 #pragma unroll
         for (int v = 0; v < 4; ++v) acc[mt][rt][v] = 0.0f;
 
-    // One block, whose loads are issued. FAR: MXFP4 rows of any scales; else false, with nothing
-    // taken, where a row's scales are too far apart or too large or small.
-    const auto block = [&](int b, auto far_tag) -> bool {
-      constexpr bool FAR = decltype(far_tag)::value;
-      wait_vmcnt<kAfterX>();  // the block's activations are in LDS (its scales and codes may not be here yet)
+    // codes of row tile rt into operand order: chunk x of row r at chunk x ^ ((r >> 1) & 7)
+    const auto stage = [&](int b, int rt, uint4 (&w)[2]) {
+      uint8_t* const p = rt % NB ? bt1 : bt0;
+      const int wr = lane >> 3;
       wave_lds_fence();
-      v4i aop[MX ? 1 : MTT][2][2];
-      uint2 xa[MX ? MTT : 1][2][2], xb[MX ? MTT : 1][2][2];
 #pragma unroll
-      for (int mt = 0; mt < MTT; ++mt)
+      for (int c = 0; c < 2; ++c)
+        *reinterpret_cast<uint4*>(p + (8 * c + wr) * 128 + (((lane & 7) ^ (((8 * c + wr) >> 1) & 7)) * 16)) = W[rt][c];
+      wave_lds_fence();
+      const int rs = (li >> 1) & 7;
+      w[0] = *reinterpret_cast<const uint4*>(p + li * 128 + ((g ^ rs) * 16));
+      w[1] = *reinterpret_cast<const uint4*>(p + li * 128 + (((4 + g) ^ rs) * 16));
+      fetch_w(b + kDmWaves, rt);
+    };
+    if constexpr (MX) {
+      // One block, whose loads are issued. FAR: rows of any scales; else false, with nothing taken,
+      // where a row's scales are too far apart or too large or small.
+      const auto block = [&](int b, auto far_tag) -> bool {
+        constexpr bool FAR = decltype(far_tag)::value;
+        wait_vmcnt<kAfterX>();  // the block's activations are in LDS (its scales and codes may not be here yet)
+        wave_lds_fence();
+        uint2 xa[MTT][2][2], xb[MTT][2][2];
 #pragma unroll
-        for (int c = 0; c < 2; ++c)
+        for (int mt = 0; mt < MTT; ++mt)
 #pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const uint8_t* const row = sa + (mt * 16 + li) * 256;
-            if constexpr (MX) {
+          for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              const uint8_t* const row = sa + (mt * 16 + li) * 256;
               const int col = 2 * (4 * c + 2 * h + (g >> 1));
               xa[mt][c][h] = *reinterpret_cast<const uint2*>(row + ((col ^ li) * 16) + 8 * (g & 1));
               xb[mt][c][h] = *reinterpret_cast<const uint2*>(row + (((col + 1) ^ li) * 16) + 8 * (g & 1));
-            } else {
-              aop[mt][c][h] = *reinterpret_cast<const v4i*>(row + (((2 * (4 * c + g) + h) ^ li) * 16));
             }
-          }
-      ssd[lane] = __float_as_uint(dd);
-      if constexpr (!MX) ssd[64 + lane] = sc;
-      wave_lds_fence();
-      float4 d4[MTT];
+        ssd[lane] = __float_as_uint(dd);
+        wave_lds_fence();
+        float4 d4[MTT];
 #pragma unroll
-      for (int mt = 0; mt < MTT; ++mt) d4[mt] = *reinterpret_cast<const float4*>(&ssd[mt * 16 + 4 * g]);
-      uint32_t scr[RT];
-      if constexpr (!MX) {
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) scr[rt] = ssd[64 + rt * 16 + li];
-      }
-      wave_lds_fence();
-      __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));  // LDS reads done: the area may be refilled
-      wave_lds_fence();
-      // MXFP4: the block's scales, and (a bit per row tile) whether those of the lane's row span
-      // more than 2^8 (the unit's sums need not be exact then) or any is outside 2^+-63 (they
-      // could overflow, or lose bits that d brings back). Halves: E and 255 - E, maxima over the
-      // row's eight chunks.
-      uint32_t es[MX ? RT : 1][2], far = 0;
-      uint32_t top[MX ? RT : 1];  // the row's largest
-      if constexpr (MX) {
+        for (int mt = 0; mt < MTT; ++mt) d4[mt] = *reinterpret_cast<const float4*>(&ssd[mt * 16 + 4 * g]);
+        wave_lds_fence();
+        __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));  // LDS reads done: the area may be refilled
+        wave_lds_fence();
+        // The block's scales, and (a bit per row tile) whether those of the lane's row span more
+        // than 2^8 (the unit's sums need not be exact then) or any is outside 2^+-63 (they could
+        // overflow, or lose bits that d brings back). Halves: E and 255 - E, maxima over the row's
+        // eight chunks.
+        uint32_t es[RT][2], far = 0;
+        uint32_t top[RT];  // the row's largest
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
           es[rt][0] = E[rt][0];
@@ -300,26 +303,11 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
           far |= (uint32_t)((rt * 16 + li < nrows) & ((top[rt] > 190u) | (low < 64u) | (top[rt] - low > 8u))) << rt;
         }
         if (!FAR && __any(far)) return false;
-      }
-      fetch_x(b + kDmWaves);
-      __builtin_amdgcn_sched_barrier(0);
-      fetch_sd(b + kDmWaves);
-      // codes of row tile rt into operand order: chunk x of row r at chunk x ^ ((r >> 1) & 7)
-      uint4 wt[2][2];
-      const auto stage_w = [&](int rt) {
-        uint8_t* const p = rt % NB ? bt1 : bt0;
-        const int wr = lane >> 3;
-        wave_lds_fence();
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-          *reinterpret_cast<uint4*>(p + (8 * c + wr) * 128 + (((lane & 7) ^ (((8 * c + wr) >> 1) & 7)) * 16)) = W[rt][c];
-        wave_lds_fence();
-        const int rs = (li >> 1) & 7;
-        wt[rt & 1][0] = *reinterpret_cast<const uint4*>(p + li * 128 + ((g ^ rs) * 16));
-        wt[rt & 1][1] = *reinterpret_cast<const uint4*>(p + li * 128 + (((4 + g) ^ rs) * 16));
-        fetch_w(b + kDmWaves, rt);
-      };
-      if constexpr (MX) {
+        fetch_x(b + kDmWaves);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch_sd(b + kDmWaves);
+        uint4 wt[2][2];
+        const auto stage_w = [&](int rt) { stage(b, rt, wt[rt & 1]); };
         v8i alo[MTT][2], ahi[MTT][2];
 #pragma unroll
         for (int mt = 0; mt < MTT; ++mt)
@@ -454,77 +442,104 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
           }
         }
         return true;
-      }
-      stage_w(0);
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        if (rt + 1 < RT) stage_w(rt + 1);  // its LDS round trip runs beside this tile's MFMAs
-        v4i bop[NP][2][2];
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const uint4 w = wt[rt & 1][c];
-          int u[8];
-          if constexpr (FMT == 1) unpack64t(w.x, w.y, u);
-          else unpack16c(w, u);
-          bop[0][c][0] = v4i{u[0], u[1], u[2], u[3]};
-          bop[0][c][1] = v4i{u[4], u[5], u[6], u[7]};
-          if constexpr (FMT == 1) {
-            unpack64t(w.z, w.w, u);
-            bop[NP - 1][c][0] = v4i{u[0], u[1], u[2], u[3]};
-            bop[NP - 1][c][1] = v4i{u[4], u[5], u[6], u[7]};
-          }
-        }
-        const float s1 = f16_bits_to_f32((uint16_t)(scr[rt] & 0xFFFFu));
-        const float s2 = FMT == 1 ? f16_bits_to_f32((uint16_t)(scr[rt] >> 16)) : 0.0f;
-        v4i C[MTT][NP];
-#pragma unroll
-        for (int mt = 0; mt < MTT; ++mt)
-#pragma unroll
-          for (int p = 0; p < NP; ++p) C[mt][p] = v4i{0, 0, 0, 0};
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-          for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int mt = 0; mt < MTT; ++mt)
-#pragma unroll
-              for (int p = 0; p < NP; ++p)
-                C[mt][p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(aop[mt][c][h], bop[p][c][h], C[mt][p], 0, 0, 0);
-        // token mt * 16 + 4g + v, row rt * 16 + li: the exact block sums, then one fp32
-        // multiply-add per plane
-#pragma unroll
-        for (int mt = 0; mt < MTT; ++mt) {
-          const float dv[4] = {d4[mt].x, d4[mt].y, d4[mt].z, d4[mt].w};
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            acc[mt][rt][v] = fmaf(s1 * dv[v], (float)(C[mt][0][v] >> SH), acc[mt][rt][v]);
-            if constexpr (FMT == 1)
-              acc[mt][rt][v] = fmaf(s2 * dv[v], (float)(C[mt][NP - 1][v] >> SH), acc[mt][rt][v]);
-          }
-        }
-        if constexpr (DBG) {
-#pragma unroll
-          for (int mt = 0; mt < MTT; ++mt)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              const int tok = mt * 16 + 4 * g + v, r = rt * 16 + li;
-              if (tok < ntok && row0 + r < n) {
-                int32_t* o = isum_dbg + (((int64_t)(t0 + tok) * n + row0 + r) * kb + b) * NP;
-                o[0] = C[mt][0][v] >> SH;
-                if constexpr (FMT == 1) o[1] = C[mt][NP - 1][v] >> SH;
-              }
-            }
-        }
-      }
-      return true;
-    };
-    if constexpr (MX) {
+      };
       int b = kg;
       if constexpr (!DBG)
         while (b < kb && block(b, std::false_type{})) b += kDmWaves;
       for (; b < kb; b += kDmWaves) block(b, std::true_type{});  // (on from the first such block)
     } else {
-      for (int b = kg; b < kb; b += kDmWaves) block(b, std::false_type{});
+      for (int b = kg; b < kb; b += kDmWaves) {
+        wait_vmcnt<kAfterX>();  // the block's activations are in LDS (its scales and codes may not be here yet)
+        wave_lds_fence();
+        v4i aop[MTT][2][2];
+#pragma unroll
+        for (int mt = 0; mt < MTT; ++mt)
+#pragma unroll
+          for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              const uint8_t* const row = sa + (mt * 16 + li) * 256;
+              aop[mt][c][h] = *reinterpret_cast<const v4i*>(row + (((2 * (4 * c + g) + h) ^ li) * 16));
+            }
+        ssd[lane] = __float_as_uint(dd);
+        ssd[64 + lane] = sc;
+        wave_lds_fence();
+        float4 d4[MTT];
+#pragma unroll
+        for (int mt = 0; mt < MTT; ++mt) d4[mt] = *reinterpret_cast<const float4*>(&ssd[mt * 16 + 4 * g]);
+        uint32_t scr[RT];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) scr[rt] = ssd[64 + rt * 16 + li];
+        wave_lds_fence();
+        __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));  // LDS reads done: the area may be refilled
+        wave_lds_fence();
+        fetch_x(b + kDmWaves);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch_sd(b + kDmWaves);
+        uint4 wt[2][2];
+        const auto stage_w = [&](int rt) { stage(b, rt, wt[rt & 1]); };
+        stage_w(0);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+          if (rt + 1 < RT) stage_w(rt + 1);  // its LDS round trip runs beside this tile's MFMAs
+          v4i bop[NP][2][2];
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            const uint4 w = wt[rt & 1][c];
+            int u[8];
+            if constexpr (FMT == 1) unpack64t(w.x, w.y, u);
+            else unpack16c(w, u);
+            bop[0][c][0] = v4i{u[0], u[1], u[2], u[3]};
+            bop[0][c][1] = v4i{u[4], u[5], u[6], u[7]};
+            if constexpr (FMT == 1) {
+              unpack64t(w.z, w.w, u);
+              bop[NP - 1][c][0] = v4i{u[0], u[1], u[2], u[3]};
+              bop[NP - 1][c][1] = v4i{u[4], u[5], u[6], u[7]};
+            }
+          }
+          const float s1 = f16_bits_to_f32((uint16_t)(scr[rt] & 0xFFFFu));
+          const float s2 = FMT == 1 ? f16_bits_to_f32((uint16_t)(scr[rt] >> 16)) : 0.0f;
+          v4i C[MTT][NP];
+#pragma unroll
+          for (int mt = 0; mt < MTT; ++mt)
+#pragma unroll
+            for (int p = 0; p < NP; ++p) C[mt][p] = v4i{0, 0, 0, 0};
+#pragma unroll
+          for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+              for (int mt = 0; mt < MTT; ++mt)
+#pragma unroll
+                for (int p = 0; p < NP; ++p)
+                  C[mt][p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(aop[mt][c][h], bop[p][c][h], C[mt][p], 0, 0, 0);
+          // token mt * 16 + 4g + v, row rt * 16 + li: the exact block sums, then one fp32
+          // multiply-add per plane
+#pragma unroll
+          for (int mt = 0; mt < MTT; ++mt) {
+            const float dv[4] = {d4[mt].x, d4[mt].y, d4[mt].z, d4[mt].w};
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              acc[mt][rt][v] = fmaf(s1 * dv[v], (float)(C[mt][0][v] >> SH), acc[mt][rt][v]);
+              if constexpr (FMT == 1)
+                acc[mt][rt][v] = fmaf(s2 * dv[v], (float)(C[mt][NP - 1][v] >> SH), acc[mt][rt][v]);
+            }
+          }
+          if constexpr (DBG) {
+#pragma unroll
+            for (int mt = 0; mt < MTT; ++mt)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) {
+                const int tok = mt * 16 + 4 * g + v, r = rt * 16 + li;
+                if (tok < ntok && row0 + r < n) {
+                  int32_t* o = isum_dbg + (((int64_t)(t0 + tok) * n + row0 + r) * kb + b) * NP;
+                  o[0] = C[mt][0][v] >> SH;
+                  if constexpr (FMT == 1) o[1] = C[mt][NP - 1][v] >> SH;
+                }
+              }
+          }
+        }
+      }
     }
     // (the last, empty refills of the activations have landed before the area is reused)
     wait_vmcnt<0>();
@@ -583,6 +598,9 @@ void launch_gemv_mfma(int fmt, const uint8_t* codes, const void* scales, int n, 
   const int rt = isum_dbg ? std::min(tiles->rt, 2) : tiles->rt;
   const int64_t ntt = ttiles(mtt);
   // several token tiles: a multiple of 8 row tiles, so that a row tile's workgroups share an XCD
+  // (520 x 16384, 200 tokens: 16.9 us, 22.1 without; the workgroups past n run their blocks for
+  // nothing: returning at once takes 15.8 there, but the wait for n ahead of the first loads 13.7
+  // for 13.1 at 2048 x 4096, 509 tokens)
   const int64_t gx = ntt > 1 ? (wgs(rt) + 7) / 8 * 8 : wgs(rt);
   const dim3 grid((unsigned)gx, (unsigned)(ntt < 16384 ? ntt : 16384));
 #define TQ_DM(F, M, R, D) \
