@@ -148,9 +148,9 @@ __device__ __forceinline__ void dm_combine(const uint8_t* s_wave, int lnw, int64
 }
 
 // FMT 0: folded codes, f16 scales. FMT 1: two planes, f16 scale pairs. FMT 2: MXFP4, e8m0
-// scales. DBG: the instance that
-// stores the exact block sums (so that the others carry no store addresses).
-template <int FMT, int MTT, int RT, bool DBG>
+// scales. DBG: the instance that stores the exact block sums (so that the others carry no store
+// addresses). NT: nontemporal weight loads.
+template <int FMT, int MTT, int RT, bool DBG, bool NT>
 __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(MTT == 1 && (FMT != 2 || RT == 1) && !DBG ? 4 : 2))) void k_gemv_mfma(
     const uint8_t* __restrict__ codes, const void* __restrict__ scales, int n, int kb, int lnw,
     const int8_t* __restrict__ q, const float* __restrict__ d, int t, float* __restrict__ y,
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
   using S = DmShape<MTT, RT>;
   constexpr bool MX = FMT == 2;
   constexpr int NP = FMT == 1 ? 2 : 1, SH = FMT == 1 ? 6 : 4, SB = MX ? 8 : (FMT == 1 ? 4 : 2);
-  constexpr int AUX = MTT == 1 ? kBufNT : 0;  // up to 16 tokens each weight byte is read once
+  constexpr int AUX = NT ? kBufNT : 0;
   constexpr int NB = MTT <= 2 && RT > 1 ? 2 : 1;  // row tiles in LDS at once
   __shared__ __attribute__((aligned(16))) uint8_t s_wave[kDmWaves * S::kWave];
   // (one variable per area, so that the compiler can tell them from the one being refilled)
@@ -603,8 +603,13 @@ void launch_gemv_mfma(int fmt, const uint8_t* codes, const void* scales, int n, 
   // for 13.1 at 2048 x 4096, 509 tokens)
   const int64_t gx = ntt > 1 ? (wgs(rt) + 7) / 8 * 8 : wgs(rt);
   const dim3 grid((unsigned)gx, (unsigned)(ntt < 16384 ? ntt : 16384));
+  // 16-token tiles read the weights nontemporally where few tiles read them again (each call
+  // another matrix, folded, us so and not: 512 x 16384, 64 tokens 9.6 and 9.9; 2048 x 4096, 24 tokens
+  // 4.65 and 4.9; 512 x 4096, 100 tokens 4.6 and 4.2; 256 x 4096, 300 tokens 6.4 and 5.9)
+  const bool nt = ntt <= 4;
 #define TQ_DM(F, M, R, D) \
-  dm_launch(k_gemv_mfma<F, M, R, D>, grid, st, events, codes, scales, n, kb, lnw, q, d, t, y, isum_dbg)
+  dm_launch(nt && M == 1 && !D ? k_gemv_mfma<F, M, R, D, M == 1 && !D> : k_gemv_mfma<F, M, R, D, false>, grid, st, events, \
+            codes, scales, n, kb, lnw, q, d, t, y, isum_dbg)
   switch ((isum_dbg ? 1000 : 0) + fmt * 100 + mtt * 10 + rt) {
     case 11: TQ_DM(0, 1, 1, false); break;
     case 12: TQ_DM(0, 1, 2, false); break;
