@@ -23,13 +23,13 @@ struct Api {
   decltype(&tq_moe_grouped) moe_grouped;
 } api;
 
-// A plain contiguous device tensor of this type and shape (dims: its sizes; nd < 0: any).
+// A plain contiguous device tensor of this type and shape (dims: its nd sizes; dev_any: of any).
 struct Arg {
   void* ptr = nullptr;
   bool ok = false;
 };
 
-Arg dev(PyObject* o, at::ScalarType dt, int nd, const int64_t* dims) {
+Arg dev_sizes(PyObject* o, at::ScalarType dt, int nd, const int64_t* dims) {
   Arg a;
   if (!THPVariable_CheckExact(o)) return a;
   const at::Tensor& t = THPVariable_Unpack(o);
@@ -47,8 +47,10 @@ Arg dev(PyObject* o, at::ScalarType dt, int nd, const int64_t* dims) {
 template <typename... D>
 Arg dev(PyObject* o, at::ScalarType dt, D... d) {
   const int64_t dims[] = {(int64_t)d...};
-  return dev(o, dt, (int)sizeof...(d), dims);
+  return dev_sizes(o, dt, (int)sizeof...(d), dims);
 }
+
+Arg dev_any(PyObject* o, at::ScalarType dt) { return dev_sizes(o, dt, -1, nullptr); }
 
 bool to_i64(PyObject* o, int64_t* v) {
   if (!PyLong_CheckExact(o)) return false;
@@ -191,7 +193,7 @@ PyObject* py_moe_grouped(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
       if (!c[p].ok || !s[p].ok) return false;
     }
     const Arg x = dev(a[5], kF32, t, H), idx = dev(a[6], kI32, t, topk), w = dev(a[7], kF32, t, topk), out = dev(a[8], kF32, t, H),
-              ws = dev(a[9], kU8, -1, nullptr);
+              ws = dev_any(a[9], kU8);
     if (!x.ok || !idx.ok || !w.ok || !out.ok || !ws.ok) return false;
     tq_experts ex{};
     ex.n_experts = (int32_t)E;

@@ -33,7 +33,13 @@ def test_weights_objects_that_describe_themselves_keep_the_python_path(monkeypat
     assert not tq._native(None, tq.TqExpertRecords(1, 256, 256, None), tq.TqExperts)
 
 
-GPU_CALLS = ["quantize_act", "gemv", "gemv_f32", "gemv2", "gemv_mx"]
+GPU_CALLS = ["quantize_act", "gemv", "gemv_f32", "gemv2", "gemv_mx", "moe_grouped"]
+
+
+def moe(*a):
+    """tq_moe_grouped on the plain tensors of a TqExperts (codes, scales) and the call's own."""
+    tq.tq_moe_grouped(tq.TqExperts(4, 512, 256, a[:3], a[3:6]), *a[6:])
+    a[-1].zero_()  # (the workspace's contents are nobody's)
 
 
 def args_of(name):
@@ -52,6 +58,14 @@ def args_of(name):
         return tq.tq_gemv, [tq.TqMatrix(n, k, codes, s), q, d, b, y]
     if name == "gemv_f32":
         return tq.tq_gemv_f32, [tq.TqMatrix(n, k, codes, s), x, y, q, d, b]
+    if name == "moe_grouped":
+        experts = 4
+        shapes = [(256, 2), (256, 2), (512, 1)]
+        codes = [torch.randint(0, 256, (experts, r, kb, 128), dtype=torch.uint8, device="cuda", generator=g) & 0x33 for r, kb in shapes]
+        scales = [torch.full((experts, r, kb), 0x2C00, dtype=torch.int16, device="cuda") for r, kb in shapes]
+        idx = torch.tensor([[0, 2], [3, 2]], dtype=torch.int32, device="cuda")
+        ws = tq.moe_workspace(tq.TqExperts(experts, 512, 256, tuple(codes), tuple(scales)), t, 2)
+        return moe, [*codes, *scales, x, idx, torch.rand((t, 2), device="cuda", generator=g), torch.zeros_like(x), ws]
     if name == "gemv2":
         return tq.tq_gemv2, [tq.TqMatrix2(n, k, codes, s[:, :, None].repeat(1, 1, 2).contiguous()), q, d, y]
     return tq.tq_gemv_mx, [tq.TqMatrixMx(n, k, codes, torch.full((n, 16), 120, dtype=torch.uint8, device="cuda")), q, d, y]
@@ -77,8 +91,8 @@ def test_native_and_python_paths_agree(name, monkeypatch):
     for i, v in enumerate(args):
         if isinstance(v, torch.Tensor):
             variants += [lambda a, i=i: a[:i] + [a[i].double()] + a[i + 1:],      # type
-                         lambda a, i=i: a[:i] + [a[i][:, :1]] + a[i + 1:],        # shape, and strides where wider
-                         lambda a, i=i: a[:i] + [a[i].t()] + a[i + 1:],
+                         lambda a, i=i: a[:i] + [a[i].narrow(-1, 0, 1)] + a[i + 1:],  # shape, and strides where wider
+                         lambda a, i=i: a[:i] + [a[i].transpose(0, -1)] + a[i + 1:],
                          lambda a, i=i: a[:i] + [a[i].cpu()] + a[i + 1:],
                          lambda a, i=i: a[:i] + [a[i][None]] + a[i + 1:],
                          lambda a, i=i: a[:i] + [None] + a[i + 1:]]
