@@ -11,6 +11,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from dataclasses import dataclass
 
 import numpy as np
@@ -127,7 +128,8 @@ try:
     from . import _tqpy as _fast
     _fast.bind(*[ctypes.cast(getattr(_L, n), _vp).value for n in (
         "tq_quantize_act", "tq_gemv", "tq_gemv_f32", "tq_gemv2", "tq_gemv_mx", "tq_moe_grouped")])
-except ImportError:
+except ImportError as _e:
+    warnings.warn(f"_tqpy.so is not built or does not load ({_e}): calls go through ctypes, about 5 us more each", RuntimeWarning)
     _fast = None
 
 

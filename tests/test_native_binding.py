@@ -1,11 +1,14 @@
 """The native half of the Python binding (_tqpy.so) takes exactly the calls that the Python
 path takes, and leaves every other to it."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
+from paper_2608_08910_amd import _tqpy as fast  # (built with the library: its absence is a failure)
 from paper_2608_08910_amd import tq
-
-fast = pytest.importorskip("paper_2608_08910_amd._tqpy")
 
 
 def test_native_functions_leave_what_they_do_not_take():
@@ -31,6 +34,13 @@ def test_weights_objects_that_describe_themselves_keep_the_python_path(monkeypat
     assert tq._native(None, m, tq.TqMatrix) and tq._native(None) and not tq._native(0, m, tq.TqMatrix)
     assert not tq._native(None, type("Own", (tq.TqMatrix,), {})(1, 256, None, None), tq.TqMatrix)
     assert not tq._native(None, tq.TqExpertRecords(1, 256, 256, None), tq.TqExperts)
+
+
+def test_missing_native_half_is_reported():
+    code = ("import sys, warnings; sys.modules['paper_2608_08910_amd._tqpy'] = None; warnings.simplefilter('error')\n"
+            "try:\n    from paper_2608_08910_amd import tq\nexcept RuntimeWarning as e:\n    print(e)")
+    r = subprocess.run([sys.executable, "-c", code], cwd=os.path.dirname(os.path.dirname(tq.__file__)), capture_output=True, text=True)
+    assert "_tqpy.so is not built" in r.stdout, r.stdout + r.stderr
 
 
 GPU_CALLS = ["quantize_act", "gemv", "gemv_f32", "gemv2", "gemv_mx", "moe_grouped"]
