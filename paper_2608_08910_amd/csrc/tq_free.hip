@@ -85,10 +85,6 @@ __device__ __forceinline__ int group16_sum(int v) {
   return v + __builtin_amdgcn_update_dpp(0, v, kDppRowRor8, 0xf, 0xf, false);
 }
 
-// A weight's plane pair for |w| (both trits change sign with w) as one word: bits 31:30 t2 and
-// 29:28 t1 in two's complement; below them what a sum over the block's weights counts: bit 0
-// t1 != 0, bit 6 t2 != 0, bit 12 trits of opposite direction, bit 18 of the same, relative to
-// the signs of (a1, a2).
 // a * b + c in one instruction (24-bit operands; the compiler splits it into a multiply and a
 // three-operand add)
 __device__ __forceinline__ int mad24(int a, int b, int c) {
@@ -97,6 +93,10 @@ __device__ __forceinline__ int mad24(int a, int b, int c) {
   return r;
 }
 
+// A weight's plane pair for |w| (both trits change sign with w) as one word: bits 31:30 t2 and
+// 29:28 t1 in two's complement; below them what a sum over the block's weights counts: bit 0
+// t1 != 0, bit 6 t2 != 0, bit 12 trits of opposite direction, bit 18 of the same, relative to
+// the signs of (a1, a2).
 constexpr uint32_t kPairMask = 0xF0000000u;
 __device__ __forceinline__ uint32_t trit2(int t) { return (uint32_t)t & 3u; }
 // the pair's four top bits for w of either sign
@@ -148,12 +148,11 @@ __device__ __forceinline__ uint32_t level_pair(uint32_t aw, const Levels& L) {
   return aw >= L.T[3] ? L.K[3] : k;
 }
 
-// One lane's share of a block: its pairs (t1 in bits 1:0, t2 in bits 3:2), the scale pair and
-// the plane steps.
+// A block's scale pair at the alternation's end and its plane steps.
 struct FreeFit {
-  uint32_t x[kFreeE];
-  uint16_t h1, h2;
+  float a1, a2;
   int it;
+  float amax;  // the block's largest magnitude (the threshold step's)
 };
 
 // The alternation for any block (every lane of the wave): scale sums in the pairwise-halving
@@ -162,7 +161,6 @@ __device__ __forceinline__ void free_fit_general(const float (&v)[kFreeE], const
                                                  int max_iter, FreeFit& F) {
 #pragma clang fp contract(off)
   int t1[kFreeE], t2[kFreeE];
-  uint16_t h1 = 0, h2 = 0;
   // the tied fit: weight u + 32m in the low nibble of byte 16m + u, u + 32m + 16 in the high
 #pragma unroll
   for (int m = 0; m < kFreeE / 2; ++m) {
@@ -222,18 +220,8 @@ __device__ __forceinline__ void free_fit_general(const float (&v)[kFreeE], const
       done = same || it == max_iter;
     }
   }
-  if (live) {
-    h1 = f16_sat(a1);
-    h2 = f16_sat(a2);
-    free_plane_step(v, f16_bits_to_f32(h1), f16_bits_to_f32(h2), t1, t2);
-  } else {
-#pragma unroll
-    for (int j = 0; j < kFreeE; ++j) t1[j] = t2[j] = 0;
-  }
-#pragma unroll
-  for (int j = 0; j < kFreeE; ++j) F.x[j] = trit2(t1[j]) | (trit2(t2[j]) << 2);
-  F.h1 = h1;
-  F.h2 = h2;
+  F.a1 = a1;
+  F.a2 = a2;
   F.it = it;
 }
 
@@ -336,16 +324,10 @@ __device__ __forceinline__ bool free_fit_levels(const float (&v)[kFreeE], const 
     sb = (c13 >> 16) - (c02 >> 16);
     sb = (int)(__float_as_uint(a1) ^ __float_as_uint(a2)) < 0 ? -sb : sb;
   }
+  F.a1 = a1;
+  F.a2 = a2;
   F.it = it;
-  F.h1 = live ? f16_sat(a1) : 0;
-  F.h2 = live ? f16_sat(a2) : 0;
-  const Levels L = make_levels(f16_bits_to_f32(F.h1), f16_bits_to_f32(F.h2), amax);
-  if (!__all(L.ok | !live)) return false;
-  const uint32_t keep = live ? kPairMask : 0u;
-#pragma unroll
-  for (int j = 0; j < kFreeE; ++j) {
-    F.x[j] = pair_signed((level_pair(__float_as_uint(fabsf(v[j])), L) & keep) >> 28, v[j]);
-  }
+  F.amax = amax;
   return true;
 }
 
@@ -353,7 +335,11 @@ __device__ __forceinline__ bool free_fit_levels(const float (&v)[kFreeE], const 
 // threshold step is 17 operations (compares and selects of the pair, four whole-number
 // multiply-adds, the count, the change test), where the nine-candidate search with its products takes about 60 operations:
 // 2048 x 4096 82 us, the search alone 242. (A wave runs until its slowest of four blocks stops:
-// 6.9 iterations, 3.5 a block on average.)
+// 6.9 iterations, 3.5 a block on average.) A wave that falls back in the
+// alternation starts the search over and pays for both; where only the rounded scales are too
+// close, only the last step is searched (weights of 2^-24, whose scales are an ulp or two of f16's
+// least: 112 us, 366 starting over, the search alone 306). All kinds of blocks side by side 131 us
+// (171, 198), weights over many orders of magnitude 75 (123, 136), an outlier a block 60 (63, 177).
 __global__ __launch_bounds__(256) void k_free_quantize(const float* __restrict__ w, int64_t nblocks, int max_iter,
                                                        const uint8_t* __restrict__ tcodes,
                                                        const uint16_t* __restrict__ tscales,
@@ -372,7 +358,24 @@ __global__ __launch_bounds__(256) void k_free_quantize(const float* __restrict__
   const float s = f16_bits_to_f32(tscales[blk]);
   const uint8_t* cb = tcodes + blk * 128;
   FreeFit F;
-  if (!free_fit_levels(v, cb, s, grp, u, max_iter, F)) free_fit_general(v, cb, s, grp, u, max_iter, F);
+  const bool lv = free_fit_levels(v, cb, s, grp, u, max_iter, F);
+  if (!lv) free_fit_general(v, cb, s, grp, u, max_iter, F);
+  // the planes of the rounded scales: pairs with t1 in bits 1:0, t2 in bits 3:2
+  const bool live = s != 0.0f;
+  const uint16_t h1 = live ? f16_sat(F.a1) : 0, h2 = live ? f16_sat(F.a2) : 0;
+  uint32_t x[kFreeE];
+  const Levels L = make_levels(f16_bits_to_f32(h1), f16_bits_to_f32(h2), lv ? F.amax : 0.0f);
+  if (lv && __all(L.ok | !live)) {
+#pragma unroll
+    for (int j = 0; j < kFreeE; ++j) x[j] = pair_signed(level_pair(__float_as_uint(fabsf(v[j])), L) >> 28, v[j]);
+  } else {
+    int t1[kFreeE], t2[kFreeE];
+    free_plane_step(v, f16_bits_to_f32(h1), f16_bits_to_f32(h2), t1, t2);
+#pragma unroll
+    for (int j = 0; j < kFreeE; ++j) x[j] = trit2(t1[j]) | (trit2(t2[j]) << 2);
+  }
+#pragma unroll
+  for (int j = 0; j < kFreeE; ++j) x[j] = live ? x[j] : 0u;
   // pack: weight u + 16j is column 32 (j / 2) + 16 (j % 2) + 4 (u / 4) + (u % 4) of its
   // block, i.e. plane p's dword 4 (j / 2) + 2p + (j % 2), byte u % 4, bits 2 (u / 4). The four
   // lanes of a byte (u, u ^ 4, u ^ 8, u ^ 12) join their bits (16 bytes a plane, four j to a
@@ -384,7 +387,7 @@ __global__ __launch_bounds__(256) void k_free_quantize(const float* __restrict__
     for (int i = 0; i < kFreeE / 4; ++i) {
       uint32_t z = 0;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) z |= ((F.x[4 * i + k] >> (2 * p)) & 3u) << (8 * k);
+      for (int k = 0; k < 4; ++k) z |= ((x[4 * i + k] >> (2 * p)) & 3u) << (8 * k);
       z <<= 2 * q4;
       z |= (uint32_t)lane_xor_i<4>((int)z);
       z |= (uint32_t)lane_xor_i<8>((int)z);
@@ -396,7 +399,7 @@ __global__ __launch_bounds__(256) void k_free_quantize(const float* __restrict__
   if (t < 128 && blk0 + (t >> 3) < nblocks)
     reinterpret_cast<uint4*>(codes2 + (blk0 + (t >> 3)) * 128)[t & 7] = reinterpret_cast<const uint4*>(s_w[t >> 3])[t & 7];
   if (u == 0 && real) {
-    scales2[blk] = (uint32_t)F.h1 | ((uint32_t)F.h2 << 16);
+    scales2[blk] = (uint32_t)h1 | ((uint32_t)h2 << 16);
     if (iters) iters[blk] = (uint8_t)F.it;
   }
 }

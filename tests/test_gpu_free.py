@@ -98,6 +98,16 @@ def test_free_thresholds_and_search_agree_with_the_oracle(tq, oracle, kind):
     check(tq, oracle, w, max_iter=3)
 
 
+@pytest.mark.parametrize("e", [-25, -24, -23, -20])
+def test_free_last_step_alone_by_search(tq, oracle, e):
+    # scales of a few ulps of f16's least: well apart in the alternation, equal or zero once rounded
+    rng = np.random.default_rng(-e)
+    w = (rng.standard_normal((21, 1280)) * 2.0 ** e).astype(np.float32)
+    w[5:9] *= 2.0 ** 20  # (blocks of both kinds in a wave)
+    announce(f"free last step 2^{e}")
+    check(tq, oracle, w)
+
+
 def test_free_full_matrix_deterministic(tq, oracle):
     c = gen.QUANT_CONFIG
     w = gen.float_weights(gen.SEED, 0, c["n"], c["k"])
