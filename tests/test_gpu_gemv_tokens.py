@@ -250,3 +250,37 @@ def test_mx_loses_no_precision(tq, n, k, t, e_lo, e_hi):
     w = DOUBLED.cuda()[c4].view(n, k // 32, 32) * torch.exp2(e8.double() - 128).view(n, k // 32, 1)
     r = (q.double().view(t, k // 256, 256) * d.double().view(t, -1, 1)).view(t, k) @ w.view(n, k).t()
     assert float((y - r).norm()) <= float((y1 - r).norm())
+
+
+@pytest.mark.parametrize("tile", list(MX_TILES))
+def test_mx_near_scales_match_the_oracle(tq, oracle, tile):
+    # the scaled unit alone, two blocks for some waves and one for the others
+    (n, t), k = MX_TILES[tile], 2304
+    announce(f"mx near scales {tile}")
+    m, call, _ = make(tq, "mxfp4", n, k, n + t, 116, 125)
+    q, d, _ = gpu_quantize(tq, np.random.default_rng(t).standard_normal((t, k)).astype(np.float32))
+    y = torch.full((t + 1, n), float("nan"), device="cuda")
+    call(q, d, y[:t], None)
+    check_mx_tokens(tq, oracle, m, q, d, y[:t])
+    assert bool(torch.isnan(y[t]).all()), "written past the last token"
+
+
+@pytest.mark.parametrize("e8", [125, 40])
+@pytest.mark.parametrize("tile", list(MX_TILES))
+def test_mx_every_code_times_every_activation(tq, tile, e8):
+    # row r: one code (r / 256) % 16 at column r % 256 of a block, zeros elsewhere; token values
+    # -127 .. 127 throughout: each product exact, on near scales and on far ones
+    (n, t), k = MX_TILES[tile], 1280
+    announce(f"mx codes x activations {tile} e8={e8}")
+    r = torch.arange(n, device="cuda")
+    code, col = (r // 256) % 16, (r * 257) % 1280
+    c4 = torch.zeros((n, k), dtype=torch.int64, device="cuda")
+    c4[r, col] = code
+    m = mx_upload(tq, c4, torch.full((n, k // 32), e8, device="cuda"))
+    d = torch.ones((t, k // 256), device="cuda")
+    for v0 in range(-127, 128, t):
+        v = torch.arange(v0, v0 + t, device="cuda").clamp(max=127)
+        y = torch.full((t, n), float("nan"), device="cuda")
+        tq.tq_gemv_mx(m, v.view(t, 1).repeat(1, k).to(torch.int8), d, y)
+        want = v.double().view(t, 1) * DOUBLED.cuda()[code] * 2.0 ** (e8 - 128)
+        assert torch.equal(y.double(), want), f"activations {v0} .. {int(v[-1])}"
