@@ -194,10 +194,11 @@ __global__ __launch_bounds__(kDmWaves * 64) __attribute__((amdgpu_waves_per_eu(M
     const __amdgpu_buffer_rsrc_t dr = make_rsrc(d + (int64_t)t0 * kb, (uint32_t)(ntok * kb * 4));
     // Block b. Activations: straight to LDS, 1 KB (token rows 4e .. 4e + 3) a load, 16-byte
     // column c of row r at column c ^ (r & 15). Weights: row 16 rt + 8c + (l >> 3), chunk
-    // l & 7. Block scales of token l and row l. Rows past n, tokens past t and blocks past kb
-    // read as zero, with no memory access. Scalar offsets stay below the resource's size (rows
-    // and blocks clamped), as its range check subtracts them; a block past kb takes kDmOob as
-    // the lane's offset.
+    // l & 7. Block scales of token l and row l. Rows past n, tokens past t and blocks past kb lie
+    // past their resource and read as zero. Scalar offsets stay below the resource's size (rows
+    // and blocks clamped), as its range check subtracts them, so a load that begins past the last
+    // row or token reads that one again for its first, whose results are not stored; a block past
+    // kb takes kDmOob as the lane's offset.
     constexpr int kAfterX = MX ? 4 * RT + 1 : 2 * RT + 2;  // loads per block issued after the activations'
     uint4 W[RT][2];
     uint32_t E[MX ? RT : 1][2];  // MXFP4: the scales of row 16 rt + li, chunks g and 4 + g (bytes: any alignment)
