@@ -282,9 +282,9 @@ static tq_status gemv_run(const tq_mat* w, const int8_t* q, const float* d, cons
   const unsigned chunks = (unsigned)((t + nt - 1) / nt);
   // Several tokens: the matrix cores, except where the VALU chunks' wave loads (1 KB each, of
   // four tokens) are too few to fill the chip and launch latency decides (k = 4096, us VALU against MFMA:
-  // 1500 rows, 4 tokens 4.0 / 4.4, 8 tokens 4.8 / 4.4; 700 rows, 8 tokens 4.0 / 4.3, 16 tokens 4.9 / 4.5;
-  // k = 256: 700 rows, 16 tokens 3.3 / 3.6, 1500 rows 4.1 / 3.8; k = 12544: 700 rows, 4 tokens 5.7 / 7.1,
-  // 8 tokens 10.1 / 7.2).
+  // 1500 rows, 4 tokens 3.3 / 3.7, 8 tokens 4.0 / 3.7; 700 rows, 8 tokens 3.2 / 3.6, 16 tokens 4.1 / 3.6;
+  // k = 256: 700 rows, 16 tokens 2.8 / 3.3, 1500 rows 3.8 / 3.4; k = 12544: 700 rows, 4 tokens 5.0 / 6.6,
+  // 8 tokens 9.2 / 6.9).
   if (t > 16 || (t > 1 && (int64_t)n * chunks * nt * nl > 4 * (nl > 2 ? 5600 : 3800))) {
     (void)hipGetLastError();
     launch_gemv_mfma(0, w->codes, w->scales, n, kb, q, d, (int)t, y, isum_dbg, (hipStream_t)stream, events);

@@ -186,9 +186,11 @@ static tq_status gemv2_run(const tq_mat2* w, const int8_t* q, const float* d, in
   const unsigned chunks = (unsigned)((t + nt - 1) / nt);
   // Several tokens: the matrix cores, except where the VALU chunks' wave loads (1 KB each, of
   // four tokens) are too few to fill the chip and launch latency decides (k = 4096, us VALU against MFMA:
-  // 700 rows, 4 tokens 3.5 / 4.3, 8 tokens 4.3 / 4.3, 16 tokens 5.3 / 4.6; k = 1024: 1500 rows, 4 tokens
-  // 3.3 / 3.6, 8 tokens 3.7 / 3.6; k = 12544: 300 rows, 4 tokens 5.6 / 7.0, 8 tokens 7.3 / 7.2).
-  if (t > 16 || (t > 1 && (int64_t)n * chunks * nt * nl > 4 * 3000)) {
+  // 700 rows, 4 tokens 2.9 / 3.8, 8 tokens 3.6 / 3.8, 16 tokens 4.4 / 3.8; k = 1024: 1500 rows, 4 tokens
+  // 2.7 / 3.2, 8 tokens 3.2 / 3.2). Rows of more than four loads take a wave a token each, so their waves
+  // count (k = 9216: 300 rows, 8 tokens 4.6 / 5.4, 12 tokens 5.4 / 5.4; k = 12544: 300 rows, 8 tokens 6.0 /
+  // 6.6, 12 tokens 7.0 / 6.5; k = 16384: 500 rows, 6 tokens 7.0 / 7.7, 8 tokens 8.5 / 7.7).
+  if (t > 16 || (t > 1 && (int64_t)n * chunks * nt * nl > (nl > 4 ? 3400 * nl : 4 * 3000))) {
     (void)hipGetLastError();
     launch_gemv_mfma(1, w->codes, w->scales, n, kb, q, d, (int)t, y, isum_dbg, (hipStream_t)stream, events);
     return check_launch("tq_gemv2");

@@ -170,8 +170,10 @@ static tq_status gemv_mx_run(const tq_mat_mx* w, const int8_t* q, const float* d
   const unsigned chunks = (unsigned)((t + nt - 1) / nt);
   // Several tokens: the matrix cores, except where the VALU chunks' wave loads (1 KB each, of
   // four tokens) are too few to fill the chip and launch latency decides (k = 4096, us VALU against MFMA:
-  // 1500 rows, 4 tokens 4.4 / 5.3, 8 tokens 5.3 / 5.3, 16 tokens 8.1 / 5.5; k = 256: 3000 rows, 4 tokens
-  // 3.4 / 4.1, 8 tokens 4.5 / 4.3; k = 12544: 700 rows, 4 tokens 6.6 / 9.2, 8 tokens 12.0 / 9.2).
+  // 1500 rows, 4 tokens 3.6 / 4.8, 8 tokens 4.3 / 4.7, 16 tokens 6.2 / 4.7; k = 2304: 1000 rows, 8 tokens
+  // 3.9 / 4.2, 1300 rows 4.6 / 4.2; k = 256: 3000 rows, 4 tokens
+  // 3.1 / 3.8, 8 tokens 4.1 / 3.8; k = 12544: 700 rows, 4 tokens 5.8 / 8.3, 8 tokens 10.1 / 8.3; scales
+  // of a span past 2^8 take the MFMA pass up to a quarter longer, unseen from here).
   if (t > 16 || (t > 1 && (int64_t)n * chunks * nt * nl > 4 * (nl > 2 ? 6400 : 4800))) {
     (void)hipGetLastError();
     launch_gemv_mfma(2, w->codes, w->scales, n, kb, q, d, (int)t, y, isum_dbg, (hipStream_t)stream, events);
